@@ -766,46 +766,45 @@ void launch_half(const rbffd_plan* p, const rbffd_fields* f, int c, bool hupd, h
 
 // ---- per-field energy (eq. 20) ---------------------------------------------
 // U_k = h^2 sum_i (E_ik^2 + eta0^2 |(H^n_ik + H^{n+1}_ik) / 2|^2) for every
-// field k, in FP64.  Pass 1: a wavefront reads one node's 64-field rows
-// (lane = field) and strides over nodes; a workgroup's four wavefronts are
-// summed in LDS into partial [block][K].  Pass 2 sums the partials of each
-// field in block order.  Both passes return at once unless the step counter
-// is a multiple of ``every``; the sample index is counter / every.
+// field k, in FP64.  Pass 1: a workgroup reads whole rows, kw = min(K, 64)
+// fields of 256 / kw nodes at a time (one thread per node and field, so
+// every lane works for narrow batches too), striding over the nodes; the
+// nodes' sums meet in LDS in node order into partial [block][K].  Pass 2: one
+// workgroup per field, its threads sum every 256th partial and meet in an
+// LDS tree (one thread per field took 0.2 ms per sample over 640 partials).
 __global__ __launch_bounds__(256) void k_benergy1(const float* E, const float* Ha, const float* Hb, int64_t N,
-                                                  int K, double wE, double wH, double* part, const int32_t* ctr,
-                                                  int every) {
-    if (*ctr % every) return;
-    __shared__ double sh[4][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int k = blockIdx.y * 64 + lane;
-    const int kk = k < K ? k : K - 1;
+                                                  int K, int kw, double wE, double wH, double* part) {
+    __shared__ double sh[256];
+    const int rows = 256 / kw, r = threadIdx.x / kw, kl = threadIdx.x % kw;
+    const int k = blockIdx.y * 64 + kl;
     double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 4 + wv; i < N; i += (int64_t)gridDim.x * 4) {
-        const double e = (double)E[i * K + kk];
-        const double hx = 0.5 * ((double)Ha[(i * 2) * K + kk] + (double)Hb[(i * 2) * K + kk]);
-        const double hy = 0.5 * ((double)Ha[(i * 2 + 1) * K + kk] + (double)Hb[(i * 2 + 1) * K + kk]);
-        acc += wE * e * e + wH * (hx * hx + hy * hy);
-    }
-    sh[wv][lane] = acc;
+    if (r < rows && k < K)
+        for (int64_t i = (int64_t)blockIdx.x * rows + r; i < N; i += (int64_t)gridDim.x * rows) {
+            const double e = (double)E[i * K + k];
+            const double hx = 0.5 * ((double)Ha[(i * 2) * K + k] + (double)Hb[(i * 2) * K + k]);
+            const double hy = 0.5 * ((double)Ha[(i * 2 + 1) * K + k] + (double)Hb[(i * 2 + 1) * K + k]);
+            acc += wE * e * e + wH * (hx * hx + hy * hy);
+        }
+    sh[threadIdx.x] = acc;
     __syncthreads();
-    if (wv == 0 && k < K) part[(int64_t)blockIdx.x * K + k] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
+    if (r == 0 && k < K) {
+        for (int q = 1; q < rows; ++q) acc += sh[q * kw + kl];
+        part[(int64_t)blockIdx.x * K + k] = acc;
+    }
 }
 
-__global__ void k_benergy2(const double* part, int nb, int K, double* out, const int32_t* ctr, int every) {
-    const int n = *ctr;
-    if (n % every) return;
-    const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k >= K) return;
+__global__ __launch_bounds__(256) void k_benergy2(const double* part, int nb, int K, double* out) {
+    __shared__ double sh[256];
+    const int k = blockIdx.x;
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += part[(int64_t)b * K + k];
-    out[(int64_t)(n / every) * K + k] = s;
-}
-
-__global__ void k_bctr_set(int32_t* ctr, int32_t v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *ctr = v;
-}
-__global__ void k_bctr_inc(int32_t* ctr) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *ctr += 1;
+    for (int b = threadIdx.x; b < nb; b += 256) s += part[(int64_t)b * K + k];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if (threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[k] = sh[0];
 }
 
 int energy_blocks(const rbffd_plan* p) {
@@ -813,27 +812,23 @@ int energy_blocks(const rbffd_plan* p) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(cap, std::min<int64_t>(1024, cdiv(p->E.N, 64))));
 }
 
-void launch_benergy(const rbffd_plan* p, const rbffd_fields* f, int c, double* out, RunWS& w, int every,
-                    hipStream_t st) {
+void launch_benergy(const rbffd_plan* p, const rbffd_fields* f, int c, double* out, RunWS& w, hipStream_t st) {
     const int o = 1 - c;
     const double wE = p->E.h * p->E.h;
     const double wH = p->eta0 * p->eta0 * wE;
     const int nb = energy_blocks(p);
     const int kc = (int)cdiv(p->K, 64);
     hipLaunchKernelGGL(k_benergy1, dim3(nb, kc), dim3(256), 0, st, (const float*)f->E[c], (const float*)f->H[c],
-                       (const float*)f->H[o], p->E.N, p->K, wE, wH, w.part, (const int32_t*)w.ctr, every);
-    hipLaunchKernelGGL(k_benergy2, dim3(kc), dim3(64), 0, st, (const double*)w.part, nb, p->K, out,
-                       (const int32_t*)w.ctr, every);
+                       (const float*)f->H[o], p->E.N, p->K, std::min(p->K, 64), wE, wH, w.part);
+    hipLaunchKernelGGL(k_benergy2, dim3(p->K), dim3(256), 0, st, (const double*)w.part, nb, p->K, out);
 }
 
-// one full step c -> o; with an energy request the sample of step n is taken
+// one full step c -> o; an energy sample (energy_out non-null) is taken
 // between the halves (E^n and both H levels are then available)
-void full_step_b(const rbffd_plan* p, const rbffd_fields* f, int c, double* energy_out, int every, RunWS* w,
-                 hipStream_t st) {
+void full_step_b(const rbffd_plan* p, const rbffd_fields* f, int c, double* energy_out, RunWS* w, hipStream_t st) {
     launch_half(p, f, c, true, st);
-    if (energy_out) launch_benergy(p, f, c, energy_out, *w, every, st);
+    if (energy_out) launch_benergy(p, f, c, energy_out, *w, st);
     launch_half(p, f, c, false, st);
-    if (energy_out) hipLaunchKernelGGL(k_bctr_inc, dim3(1), dim3(64), 0, st, w->ctr);
 }
 
 __global__ void k_field_gamma(float* gk, const double* c, int K, double fac, double gamma) {
@@ -862,7 +857,7 @@ int batched_step(const rbffd_plan* p, rbffd_fields* f, int32_t nsteps, hipStream
     if (f->eps_r) return set_err(p, RBFFD_ENOTSUP, "per-node eps_r is not supported for K-field batches");
     if (p->var.block > 256) return set_err(p, RBFFD_EINVAL, "K-field batches use at most 256 threads per workgroup");
     for (int s = 0; s < nsteps; ++s) {
-        full_step_b(p, f, f->cur, nullptr, 1, nullptr, st);
+        full_step_b(p, f, f->cur, nullptr, nullptr, st);
         f->cur = 1 - f->cur;
     }
     HIPCHK(p, hipGetLastError());
@@ -876,18 +871,22 @@ int batched_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_args* a, v
     if (p->var.block > 256) return set_err(p, RBFFD_EINVAL, "K-field batches use at most 256 threads per workgroup");
     if (a->energy_out && a->energy_every < 0) return set_err(p, RBFFD_EINVAL, "energy_every < 0");
     double* eo = (a->energy_out && a->energy_every > 0) ? a->energy_out : nullptr;
-    const int every = eo ? a->energy_every : 1;
     RunWS w = run_ws(ws);
-    if (eo) hipLaunchKernelGGL(k_bctr_set, dim3(1), dim3(64), 0, st, w.ctr, 0);
-    int s = 0;
-    if (a->use_graph) {
-        const int rc = replay_steps(
-            p, a->T, f->cur, st, [&](int c, hipStream_t cs) { full_step_b(p, f, c, eo, every, &w, cs); }, &s);
-        if (rc) return rc;
-    }
-    for (; s < a->T; ++s) {
-        full_step_b(p, f, f->cur, eo, every, &w, st);
+    for (int n = 0; n < a->T;) {
+        // plain steps up to the next energy sample (or the end)
+        const int plain = (eo ? std::min<int64_t>(a->T, cdiv(n, a->energy_every) * a->energy_every) : a->T) - n;
+        if (a->use_graph && plain >= RBFFD_GRAPH_MIN_STEPS) {
+            int done = 0;
+            const int rc = replay_steps(
+                p, plain, f->cur, st, [&](int c, hipStream_t cs) { full_step_b(p, f, c, nullptr, nullptr, cs); }, &done);
+            if (rc) return rc;
+            n += done;   // even: the buffers are back where they were
+            if (done > 0) continue;
+        }
+        const bool due = eo && n % a->energy_every == 0;
+        full_step_b(p, f, f->cur, due ? eo + (int64_t)(n / a->energy_every) * p->K : nullptr, &w, st);
         f->cur = 1 - f->cur;
+        ++n;
     }
     HIPCHK(p, hipGetLastError());
     return RBFFD_OK;

@@ -141,19 +141,14 @@ inline bool has_wall_normals(const rbffd_plan* p) {
     return p->p.bc == RBFFD_BC_PEC && (p->p.pol == RBFFD_POL_TE || p->dim == 3);
 }
 
-// ---- run workspace: FP64 reduction partials, the device step counter -------
+// ---- run workspace: FP64 reduction partials ---------------------------------
 constexpr int RED_BLOCKS = 1024;
 struct RunWS {
     double* part;       // [RED_BLOCKS * 12]
-    int32_t* ctr;
-    double* misc;
 };
 inline RunWS run_ws(void* ws) {
     RunWS w;
-    char* b = (char*)ws;
-    w.part = (double*)b;
-    w.ctr = (int32_t*)(b + RED_BLOCKS * 12 * 8);
-    w.misc = (double*)(b + RED_BLOCKS * 12 * 8 + 256);
+    w.part = (double*)ws;
     return w;
 }
 
@@ -194,13 +189,18 @@ int64_t setup_ws_bytes(const rbffd_plan* p);
 int capture_stream(const rbffd_plan* p, hipStream_t* out);
 
 // ---- HIP-graph step loop -----------------------------------------------------
-// The step loop of rbffd_run is replayed from HIP graphs: one graph of S
-// captured steps (S even, at most RBFFD_GRAPH_STEPS) replayed T / S times,
-// then one graph of the remaining whole step pairs.  rec(c, stream) records
+// Long stretches of plain steps (no sample, checkpoint, source or receiver in
+// them) are replayed from HIP graphs: one graph of S captured steps (S even,
+// at most RBFFD_GRAPH_STEPS) replayed T / S times, then one graph of the
+// remaining whole step pairs.  Shorter stretches are launched one by one:
+// capturing and instantiating a graph costs about 0.8 ms, and a replayed step
+// of the smallest node sets (51^2, two 3.7 us kernels) takes 7.2 us against
+// 8.2 us launched, so a graph pays from about 500 steps on.  rec(c, stream) records
 // one full step reading buffer set c; the buffers alternate within a graph
 // and, S being even, every replay leaves them as it found them.  *done
 // receives the number of steps replayed (even); the caller runs the rest.
 #define RBFFD_GRAPH_STEPS 64
+#define RBFFD_GRAPH_MIN_STEPS 512
 template <typename Rec>
 int replay_steps(const rbffd_plan* p, int T, int cur, hipStream_t st, Rec rec, int* done) {
     *done = 0;

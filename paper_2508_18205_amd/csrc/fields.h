@@ -19,6 +19,7 @@ template <typename TS> struct Store;
 
 template <> struct Store<double> {
     using C = double;
+    __device__ __forceinline__ static double rnd(double v) { return v; }   // a value as it is stored
     __device__ __forceinline__ static double ld1(const double* p, int64_t i) { return p[i]; }
     __device__ __forceinline__ static void st1(double* p, int64_t i, double v) { p[i] = v; }
     __device__ __forceinline__ static void ld2(const double* p, int64_t i, double& x, double& y) {
@@ -44,6 +45,7 @@ template <> struct Store<double> {
 
 template <> struct Store<float> {
     using C = float;
+    __device__ __forceinline__ static float rnd(float v) { return v; }
     __device__ __forceinline__ static float ld1(const float* p, int64_t i) { return p[i]; }
     __device__ __forceinline__ static void st1(float* p, int64_t i, float v) { p[i] = v; }
     __device__ __forceinline__ static void ld2(const float* p, int64_t i, float& x, float& y) {
@@ -67,6 +69,7 @@ template <> struct Store<float> {
 
 template <> struct Store<bf16s> {
     using C = float;
+    __device__ __forceinline__ static float rnd(float v) { return bf2f(f2bf(v)); }
     __device__ __forceinline__ static float ld1(const bf16s* p, int64_t i) { return bf2f(p[i].b); }
     __device__ __forceinline__ static void st1(bf16s* p, int64_t i, float v) { p[i].b = f2bf(v); }
     __device__ __forceinline__ static void ld2(const bf16s* p, int64_t i, float& x, float& y) {

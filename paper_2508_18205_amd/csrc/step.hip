@@ -56,7 +56,60 @@ struct SA {
     const int32_t* hpool;
     const int32_t* hoff;
     int Q8, hmax;
+    // a run's receivers and soft sources, folded into the half-step kernels:
+    // the H update also records E^n at the receivers, the E update adds the
+    // sources' terms of its step
+    int n_rcv, n_src, FE, comp;
+    const int32_t* rcv;
+    void* trace;          // [n_rcv] row of the traces (TC)
+    const int32_t* src;
+    const void* samp;     // [n_src] amplitudes, [n_src] waveform row (TC)
+    const void* swave;
 };
+
+// Receivers: the H update of step n + 1 reads E^{n+1} anyway, so its first
+// n_rcv threads write the trace row of step n (a kernel of its own per step
+// took 3.6 us on the 40k-node dispersion set, 200 receivers).
+template <typename TS, typename TW>
+__device__ __forceinline__ void record_receivers(const SA<TS, TW>& a) {
+    using TC = typename Store<TS>::C;
+    for (int r = (int)(blockIdx.x * blockDim.x + threadIdx.x); r < a.n_rcv; r += (int)(gridDim.x * blockDim.x))
+        ((TC*)a.trace)[r] = Store<TS>::ld1(a.E, (int64_t)a.rcv[r] * a.FE + a.comp);
+}
+
+// Soft sources: E at node i after the bracket gains amp * wave for every
+// source on it, in source order, each sum rounded to the storage type as a
+// store would; PEC nodes stay 0.
+template <typename TS, typename TW>
+__device__ __forceinline__ typename Store<TS>::C sourced(const SA<TS, TW>& a, int64_t i, bool free_,
+                                                         typename Store<TS>::C v) {
+    using TC = typename Store<TS>::C;
+    if (!free_) return (TC)0;
+    for (int s = 0; s < a.n_src; ++s)
+        if (a.src[s] == (int32_t)i)
+            v = Store<TS>::rnd(Store<TS>::rnd(v) + ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s]);
+    return v;
+}
+// 3D: the source acts on Ez; on a curved wall (mask bit 3) E is already
+// projected on the normal n, so adding v n_z n keeps (E + v e_z) projected
+template <typename TS, typename TW>
+__device__ __forceinline__ void sourced3(const SA<TS, TW>& a, int64_t i, uint8_t m, typename Store<TS>::C& x,
+                                         typename Store<TS>::C& y, typename Store<TS>::C& z) {
+    using S = Store<TS>;
+    using TC = typename S::C;
+    for (int s = 0; s < a.n_src; ++s) {
+        if (a.src[s] != (int32_t)i) continue;
+        const TC v = ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s];
+        if (m & 8) {
+            const double* n = a.wnrm + 3 * i;
+            x = S::rnd(S::rnd(x) + v * (TC)n[2] * (TC)n[0]);
+            y = S::rnd(S::rnd(y) + v * (TC)n[2] * (TC)n[1]);
+            z = S::rnd(S::rnd(z) + v * (TC)n[2] * (TC)n[2]);
+        } else {
+            z = (m & 4) ? S::rnd(S::rnd(z) + v) : (TC)0;
+        }
+    }
+}
 
 // PEC on the in-plane E of the TEz polarisation: bit 0 / 1 of the mask keeps
 // Ex / Ey (walls normal to an axis); bit 3 marks a curved-wall node with unit
@@ -109,6 +162,7 @@ __device__ __forceinline__ typename Store<TS>::C kappa_of(const SA<TS, TW>& a, i
 // ---- 2D TMz, collocated ----------------------------------------------------
 template <typename TS, typename TW>
 __global__ __launch_bounds__(512) void k_h2(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -240,7 +294,7 @@ __global__ __launch_bounds__(512) void k_e2(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = (a.nomask || (a.emask[i] & 1)) ? e0 + k * (cu + (TC)a.g * ve) : (TC)0;
+        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
@@ -250,6 +304,7 @@ __global__ __launch_bounds__(512) void k_e2(SA<TS, TW> a) {
 // the H set.  E update: curl of H from the H set, HV of E on the E set.
 template <typename TS, typename TW>
 __global__ __launch_bounds__(512) void k_h2x(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -344,7 +399,7 @@ __global__ __launch_bounds__(512) void k_e2x(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = (a.nomask || (a.emask[i] & 1)) ? e0 + k * (cu + (TC)a.g * ve) : (TC)0;
+        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
@@ -356,6 +411,7 @@ __global__ __launch_bounds__(512) void k_e2x(SA<TS, TW> a) {
 // k_h2s / k_e2s below, for the staggered variant).
 template <typename TS, typename TW>
 __global__ __launch_bounds__(256) void k_h2xs(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     __shared__ TC part[3][4][RBFFD_TILE];
@@ -464,7 +520,7 @@ __global__ __launch_bounds__(256) void k_e2xs(SA<TS, TW> a) {
     cu = ((cu + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     ve = ((ve + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
     const TC k = kappa_of(a, i);
-    const TC v = (a.nomask || (a.emask[i] & 1)) ? e0 + k * (cu + (TC)a.g * ve) : (TC)0;
+    const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
     S::st1(a.out, i, v);
 }
 
@@ -477,6 +533,7 @@ __global__ __launch_bounds__(256) void k_e2xs(SA<TS, TW> a) {
 // sums differs.
 template <typename TS, typename TW>
 __global__ __launch_bounds__(256) void k_h2s(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -589,13 +646,14 @@ __global__ __launch_bounds__(256) void k_e2s(SA<TS, TW> a) {
     cu = ((cu + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     ve = ((ve + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
     const TC k = kappa_of(a, i);
-    const TC v = (a.nomask || (a.emask[i] & 1)) ? e0 + k * (cu + (TC)a.g * ve) : (TC)0;
+    const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
     S::st1(a.out, i, v);
 }
 
 // ---- 3D, collocated: E and H stored as (x, y, z, pad) -------------------------
 template <typename TS, typename TW>
 __global__ __launch_bounds__(512) void k_h3(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -746,7 +804,9 @@ __global__ __launch_bounds__(512) void k_e3(SA<TS, TW> a) {
         TC nx = ex0 + k * ((yHz - zHy) + G * vx);
         TC ny = ey0 + k * ((zHx - xHz) + G * vy);
         TC nz = ez0 + k * ((xHy - yHx) + G * vz);
-        wall3(a.emask[i], a.wnrm, i, nx, ny, nz);
+        const uint8_t m = a.emask[i];
+        wall3(m, a.wnrm, i, nx, ny, nz);
+        sourced3(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
 }
@@ -886,6 +946,7 @@ struct Val6 {
 
 template <typename TS, typename TW>
 __global__ __launch_bounds__(256) void k_h2l(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -1029,13 +1090,14 @@ __global__ __launch_bounds__(256) void k_e2l(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = (a.nomask || (a.emask[i] & 1)) ? e0 + k * (cu + (TC)a.g * ve) : (TC)0;
+        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
 
 template <typename TS, typename TW>
 __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3l(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sE = lds_base<TC>();                           // 3 values per entry
@@ -1187,7 +1249,9 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(SA<TS, TW> a) {
         TC nx = ex0 + k * ((yHz - zHy) + G * vx);
         TC ny = ey0 + k * ((zHx - xHz) + G * vy);
         TC nz = ez0 + k * ((xHy - yHx) + G * vz);
-        wall3(a.emask[i], a.wnrm, i, nx, ny, nz);
+        const uint8_t m = a.emask[i];
+        wall3(m, a.wnrm, i, nx, ny, nz);
+        sourced3(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
 }
@@ -1276,6 +1340,7 @@ __device__ __forceinline__ void hv_sums3(const TC* sF, const uint4* pl, const TW
 
 template <typename TS, typename TW>
 __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3p(SA<TS, TW> a) {
+    record_receivers(a);
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sF = lds_base<TC>();
@@ -1342,26 +1407,27 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(SA<TS, TW> a) {
         TC nx = e0[0] + k * ((c[3] - c[5]) + G * v[0]);
         TC ny = e0[1] + k * ((c[4] - c[1]) + G * v[1]);
         TC nz = e0[2] + k * ((c[0] - c[2]) + G * v[2]);
-        wall3(a.emask[i], a.wnrm, i, nx, ny, nz);
+        const uint8_t m = a.emask[i];
+        wall3(m, a.wnrm, i, nx, ny, nz);
+        sourced3(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
 }
 
-// ---- per-step auxiliaries (read the device step counter) --------------------
-// src: E[node] += amp * wave[n * S + s] after the bracket (PEC nodes stay 0)
+// ---- auxiliaries of a run -----------------------------------------------------
+// More sources than the E update looks through per node (kMaxFoldedSources):
+// E[node] += amp * wave in source order after the bracket, one thread.
+constexpr int kMaxFoldedSources = 16;
 template <typename TS>
 __global__ void k_source(TS* E, int FE, int comp, const uint8_t* emask, const double* wn, int S, const int32_t* node,
-                         const void* amp, const void* wave, const int32_t* ctr, int step_base) {
+                         const void* amp, const void* wave) {
     using St = Store<TS>;
     using TC = typename St::C;
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int64_t n = (int64_t)(*ctr) + step_base;
     for (int s = 0; s < S; ++s) {
         const int64_t i = node[s];
         const int64_t e = i * FE + comp;
-        TC v;
-        if (sizeof(TC) == 8) v = ((const double*)amp)[s] * ((const double*)wave)[n * S + s];
-        else v = ((const float*)amp)[s] * ((const float*)wave)[n * S + s];
+        const TC v = ((const TC*)amp)[s] * ((const TC*)wave)[s];
         if (emask[i] & 8) {
             // curved 3D wall: E is already projected on the normal n, so adding
             // the projected source v n_comp n keeps (E + v e_comp) projected
@@ -1375,44 +1441,27 @@ __global__ void k_source(TS* E, int FE, int comp, const uint8_t* emask, const do
     }
 }
 
+// the trace row of a run's last step (the earlier ones: record_receivers)
 template <typename TS>
-__global__ void k_receivers(const TS* E, int FE, int comp, int R, const int32_t* node, void* traces, const int32_t* ctr,
-                            int T) {
+__global__ void k_receivers(const TS* E, int FE, int comp, int R, const int32_t* node, void* trace) {
     using St = Store<TS>;
-    using TC = typename St::C;
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = *ctr;
-    if (r >= R || n >= T) return;
-    const TC v = St::ld1(E, (int64_t)node[r] * FE + comp);
-    if (sizeof(TC) == 8) ((double*)traces)[(int64_t)n * R + r] = (double)v;
-    else ((float*)traces)[(int64_t)n * R + r] = (float)v;
+    if (r < R) ((typename St::C*)trace)[r] = St::ld1(E, (int64_t)node[r] * FE + comp);
 }
 
-__global__ void k_ctr_set(int32_t* ctr, int32_t v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *ctr = v;
-}
-__global__ void k_ctr_inc(int32_t* ctr) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *ctr += 1;
-}
-
-// checkpoint: copy (E, H) into slot n / every when n % every == 0 (2-byte units)
-__global__ void k_ckpt(const uint16_t* E, int64_t e2, const uint16_t* H, int64_t h2, char* ck, int64_t slot_bytes,
-                       int every, const int32_t* ctr) {
-    const int n = *ctr;
-    if (n % every) return;
-    uint16_t* dst = (uint16_t*)(ck + (int64_t)(n / every) * slot_bytes);
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < e2 + h2; g += (int64_t)gridDim.x * blockDim.x)
-        dst[g] = g < e2 ? E[g] : H[g - e2];
+// checkpoint: (E, H) into one slot, E first, in units of U
+template <typename U>
+__global__ __launch_bounds__(256) void k_ckpt(const U* E, int64_t e, const U* H, int64_t h, U* slot) {
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < e + h; g += (int64_t)gridDim.x * blockDim.x)
+        slot[g] = g < e ? E[g] : H[g - e];
 }
 
 // ---- FP64 reductions --------------------------------------------------------
 
 template <typename TS>
 __global__ __launch_bounds__(256) void k_energy1(const TS* E, int64_t NE, int FE, int fe, const TS* Ha, const TS* Hb,
-                                                 int64_t NH, int FH, int fh, double wE, double wH, double* part,
-                                                 const int32_t* ctr, int every) {
+                                                 int64_t NH, int FH, int fh, double wE, double wH, double* part) {
     using St = Store<TS>;
-    if (ctr && (*ctr % every)) return;
     __shared__ double sh[256];
     double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -1435,9 +1484,7 @@ __global__ __launch_bounds__(256) void k_energy1(const TS* E, int64_t NE, int FE
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-__global__ __launch_bounds__(256) void k_reduce2(const double* part, int nparts, double* out, const int32_t* ctr,
-                                                 int every) {
-    if (ctr && (*ctr % every)) return;
+__global__ __launch_bounds__(256) void k_reduce2(const double* part, int nparts, double* out) {
     __shared__ double sh[256];
     double acc = 0.0;
     for (int i = threadIdx.x; i < nparts; i += 256) acc += part[i];
@@ -1447,7 +1494,7 @@ __global__ __launch_bounds__(256) void k_reduce2(const double* part, int nparts,
         if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[ctr ? (*ctr / every) : 0] = sh[0];
+    if (threadIdx.x == 0) out[0] = sh[0];
 }
 
 template <typename TS>
@@ -1534,9 +1581,19 @@ void fill_sa(const rbffd_plan* p, const OpBlock& o, SA<TS, TW>& a, bool hupd) {
     a.hmax = o.hmax;
 }
 
+// what a run folds into one half step (null pointers: nothing)
+struct HalfAux {
+    const int32_t* rcv = nullptr;   // H update
+    void* trace = nullptr;
+    const int32_t* src = nullptr;   // E update
+    const void* samp = nullptr;
+    const void* swave = nullptr;
+    int n_rcv = 0, n_src = 0;
+};
+
 template <typename TS, typename TW>
 void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r,
-                 hipStream_t st) {
+                 const HalfAux& x, hipStream_t st) {
     // compressed (W22) weights exist only for the 2D collocated kernels
     constexpr bool kW22 = std::is_same<TW, w22>::value;
     const OpBlock& o = hupd ? p->opH : p->opE;
@@ -1546,6 +1603,15 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
     a.H = (const TS*)H;
     a.out = (TS*)out;
     a.eps_r = hupd ? nullptr : eps_r;
+    a.FE = p->FE;
+    a.comp = p->dim == 2 ? 0 : 2;
+    a.n_rcv = x.n_rcv;
+    a.rcv = x.rcv;
+    a.trace = x.trace;
+    a.n_src = x.n_src;
+    a.src = x.src;
+    a.samp = x.samp;
+    a.swave = x.swave;
     if (p->p.pol == RBFFD_POL_TE) {
         // TEz: the Hz update runs the scalar (E-update) kernel on (Hz, E) and
         // the E update the vector (H-update) kernel on (Hz_new, E); the
@@ -1611,36 +1677,37 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
     }
 }
 
-void half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r, hipStream_t st) {
+void half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r, hipStream_t st,
+          const HalfAux& x = HalfAux()) {
     switch (p->p.fdtype) {
-        case RBFFD_F64: launch_half<double, double>(p, hupd, E, H, out, eps_r, st); break;
+        case RBFFD_F64: launch_half<double, double>(p, hupd, E, H, out, eps_r, x, st); break;
         case RBFFD_F32:
-            if (p->p.wdtype == RBFFD_W22) launch_half<float, w22>(p, hupd, E, H, out, eps_r, st);
-            else launch_half<float, float>(p, hupd, E, H, out, eps_r, st);
+            if (p->p.wdtype == RBFFD_W22) launch_half<float, w22>(p, hupd, E, H, out, eps_r, x, st);
+            else launch_half<float, float>(p, hupd, E, H, out, eps_r, x, st);
             break;
-        default: launch_half<bf16s, float>(p, hupd, E, H, out, eps_r, st); break;
+        default: launch_half<bf16s, float>(p, hupd, E, H, out, eps_r, x, st); break;
     }
 }
 
 template <typename TS>
 void launch_energy(const rbffd_plan* p, const void* E, const void* Ha, const void* Hb, double* out, RunWS& w,
-                   const int32_t* ctr, int every, hipStream_t st) {
+                   hipStream_t st) {
     const double wE = std::pow(p->E.h, p->dim);
     const double hh = p->collocated ? p->E.h : p->H.h;
     const double wH = p->eta0 * p->eta0 * std::pow(hh, p->dim);
     const int64_t nmax = std::max(p->E.N, p->H.N);
     const int nb = (int)std::min<int64_t>(RED_BLOCKS, cdiv(nmax, 256));
     hipLaunchKernelGGL(k_energy1<TS>, dim3(nb), dim3(256), 0, st, (const TS*)E, p->E.N, p->FE, p->fe_comp,
-                       (const TS*)Ha, (const TS*)Hb, p->H.N, p->FH, p->fh_comp, wE, wH, w.part, ctr, every);
-    hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(256), 0, st, w.part, nb, out, ctr, every);
+                       (const TS*)Ha, (const TS*)Hb, p->H.N, p->FH, p->fh_comp, wE, wH, w.part);
+    hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(256), 0, st, w.part, nb, out);
 }
 
 void energy(const rbffd_plan* p, const void* E, const void* Ha, const void* Hb, double* out, RunWS& w,
-            const int32_t* ctr, int every, hipStream_t st) {
+            hipStream_t st) {
     switch (p->p.fdtype) {
-        case RBFFD_F64: launch_energy<double>(p, E, Ha, Hb, out, w, ctr, every, st); break;
-        case RBFFD_F32: launch_energy<float>(p, E, Ha, Hb, out, w, ctr, every, st); break;
-        default: launch_energy<bf16s>(p, E, Ha, Hb, out, w, ctr, every, st); break;
+        case RBFFD_F64: launch_energy<double>(p, E, Ha, Hb, out, w, st); break;
+        case RBFFD_F32: launch_energy<float>(p, E, Ha, Hb, out, w, st); break;
+        default: launch_energy<bf16s>(p, E, Ha, Hb, out, w, st); break;
     }
 }
 
@@ -1690,56 +1757,84 @@ extern "C" int rbffd_half(const rbffd_plan* p, const rbffd_fields* f, int32_t wh
 }
 
 namespace {
-// One full step with every auxiliary; buffers (c -> o) fixed so it can be
-// captured.  The device counter holds the step index.
-void full_step(const rbffd_plan* p, const rbffd_fields* f, int c, const rbffd_run_args* a, RunWS& w, hipStream_t st) {
+template <typename TS>
+void launch_sources(const rbffd_plan* p, void* E, const rbffd_run_args* a, const void* wave, hipStream_t st) {
+    hipLaunchKernelGGL(k_source<TS>, dim3(1), dim3(64), 0, st, (TS*)E, p->FE, p->dim == 2 ? 0 : 2, p->E.emask, p->E.nrm,
+                       a->n_src, a->src_node, a->src_amp, wave);
+}
+template <typename TS>
+void launch_receivers(const rbffd_plan* p, const void* E, const rbffd_run_args* a, void* trace, hipStream_t st) {
+    hipLaunchKernelGGL(k_receivers<TS>, dim3((unsigned)cdiv(a->n_rcv, 64)), dim3(64), 0, st, (const TS*)E, p->FE,
+                       p->dim == 2 ? 0 : 2, a->n_rcv, a->rcv_node, trace);
+}
+template <typename U>
+void launch_ckpt(const void* E, int64_t eb, const void* H, int64_t hb, void* slot, hipStream_t st) {
+    const int64_t e = eb / (int64_t)sizeof(U), h = hb / (int64_t)sizeof(U);
+    hipLaunchKernelGGL(k_ckpt<U>, dim3((unsigned)std::min<int64_t>(2048, cdiv(e + h, 256))), dim3(256), 0, st,
+                       (const U*)E, e, (const U*)H, h, (U*)slot);
+}
+// (E, H) into one checkpoint slot, in the widest unit that every address and
+// length is a multiple of (a slot's H part starts e_bytes into it)
+void checkpoint(const void* E, int64_t eb, const void* H, int64_t hb, void* slot, hipStream_t st) {
+    const uint64_t m = (uint64_t)E | (uint64_t)H | (uint64_t)slot | (uint64_t)eb | (uint64_t)hb;
+    if (m % 16 == 0) launch_ckpt<uint4>(E, eb, H, hb, slot, st);
+    else if (m % 8 == 0) launch_ckpt<uint2>(E, eb, H, hb, slot, st);
+    else if (m % 4 == 0) launch_ckpt<uint32_t>(E, eb, H, hb, slot, st);
+    else launch_ckpt<uint16_t>(E, eb, H, hb, slot, st);
+}
+
+// One full step n (buffers c -> o) with what is due in it: the checkpoint
+// before it, the energy sample between its halves; receivers and sources are
+// part of the half-step kernels.
+void full_step(const rbffd_plan* p, const rbffd_fields* f, int c, int n, const rbffd_run_args* a, RunWS& w, hipStream_t st) {
     const int o = 1 - c;
-    const int comp = p->dim == 2 ? 0 : 2;
-    if (a->ckpt) {
+    const int64_t tb = p->p.fdtype == RBFFD_F64 ? 8 : 4;   // traces, amplitudes, waveforms
+    if (a->ckpt && n % a->ckpt_every == 0) {
         const int64_t eb = p->E.N * p->FE * (int64_t)field_elem_bytes(p->p.fdtype);
         const int64_t hb = p->H.N * p->FH * (int64_t)field_elem_bytes(p->p.fdtype);
-        hipLaunchKernelGGL(k_ckpt, dim3(1024), dim3(256), 0, st, (const uint16_t*)f->E[c], eb / 2,
-                           (const uint16_t*)f->H[c], hb / 2, (char*)a->ckpt, eb + hb, a->ckpt_every,
-                           (const int32_t*)w.ctr);
+        checkpoint(f->E[c], eb, f->H[c], hb, (char*)a->ckpt + (int64_t)(n / a->ckpt_every) * (eb + hb), st);
     }
-    half(p, true, f->E[c], f->H[c], f->H[o], nullptr, st);
-    if (a->energy_out && a->energy_every > 0)
-        energy(p, f->E[c], f->H[c], f->H[o], a->energy_out, w, w.ctr, a->energy_every, st);
-    half(p, false, f->E[c], f->H[o], f->E[o], f->eps_r, st);
-    if (a->n_src > 0) {
+    HalfAux x;
+    if (a->n_rcv > 0 && n > 0) {
+        x.n_rcv = a->n_rcv;
+        x.rcv = a->rcv_node;
+        x.trace = (char*)a->traces + (int64_t)(n - 1) * a->n_rcv * tb;
+    }
+    const void* wave = (const char*)a->src_wave + ((int64_t)n + a->step0) * a->n_src * tb;
+    const bool folded = a->n_src > 0 && a->n_src <= kMaxFoldedSources;
+    if (folded) {
+        x.n_src = a->n_src;
+        x.src = a->src_node;
+        x.samp = a->src_amp;
+        x.swave = wave;
+    }
+    half(p, true, f->E[c], f->H[c], f->H[o], nullptr, st, x);
+    if (a->energy_out && a->energy_every > 0 && n % a->energy_every == 0)
+        energy(p, f->E[c], f->H[c], f->H[o], a->energy_out + n / a->energy_every, w, st);
+    half(p, false, f->E[c], f->H[o], f->E[o], f->eps_r, st, x);
+    if (a->n_src > 0 && !folded) {
         switch (p->p.fdtype) {
-            case RBFFD_F64:
-                hipLaunchKernelGGL(k_source<double>, dim3(1), dim3(64), 0, st, (double*)f->E[o], p->FE, comp, p->E.emask,
-                                   p->E.nrm, a->n_src, a->src_node, a->src_amp, a->src_wave, w.ctr, a->step0);
-                break;
-            case RBFFD_F32:
-                hipLaunchKernelGGL(k_source<float>, dim3(1), dim3(64), 0, st, (float*)f->E[o], p->FE, comp, p->E.emask,
-                                   p->E.nrm, a->n_src, a->src_node, a->src_amp, a->src_wave, w.ctr, a->step0);
-                break;
-            default:
-                hipLaunchKernelGGL(k_source<bf16s>, dim3(1), dim3(64), 0, st, (bf16s*)f->E[o], p->FE, comp,
-                                   p->E.emask, p->E.nrm, a->n_src, a->src_node, a->src_amp, a->src_wave, w.ctr, a->step0);
+            case RBFFD_F64: launch_sources<double>(p, f->E[o], a, wave, st); break;
+            case RBFFD_F32: launch_sources<float>(p, f->E[o], a, wave, st); break;
+            default: launch_sources<bf16s>(p, f->E[o], a, wave, st);
         }
     }
-    if (a->n_rcv > 0) {
-        const dim3 g((unsigned)cdiv(a->n_rcv, 64));
+    if (a->n_rcv > 0 && n == a->T - 1) {
+        void* row = (char*)a->traces + (int64_t)n * a->n_rcv * tb;
         switch (p->p.fdtype) {
-            case RBFFD_F64:
-                hipLaunchKernelGGL(k_receivers<double>, g, dim3(64), 0, st, (const double*)f->E[o], p->FE, comp,
-                                   a->n_rcv, a->rcv_node, a->traces, w.ctr, a->T);
-                break;
-            case RBFFD_F32:
-                hipLaunchKernelGGL(k_receivers<float>, g, dim3(64), 0, st, (const float*)f->E[o], p->FE, comp, a->n_rcv,
-                                   a->rcv_node, a->traces, w.ctr, a->T);
-                break;
-            default:
-                hipLaunchKernelGGL(k_receivers<bf16s>, g, dim3(64), 0, st, (const bf16s*)f->E[o], p->FE, comp,
-                                   a->n_rcv, a->rcv_node, a->traces, w.ctr, a->T);
+            case RBFFD_F64: launch_receivers<double>(p, f->E[o], a, row, st); break;
+            case RBFFD_F32: launch_receivers<float>(p, f->E[o], a, row, st); break;
+            default: launch_receivers<bf16s>(p, f->E[o], a, row, st);
         }
     }
-    // the step counter only feeds the auxiliary kernels
-    if (a->ckpt || a->n_src > 0 || a->n_rcv > 0 || (a->energy_out && a->energy_every > 0))
-        hipLaunchKernelGGL(k_ctr_inc, dim3(1), dim3(64), 0, st, w.ctr);
+}
+
+// steps from n to the next one with a sample or checkpoint due (or to T)
+int plain_steps(const rbffd_run_args* a, int n) {
+    int e = a->T;
+    if (a->ckpt) e = std::min(e, (int)cdiv(n, a->ckpt_every) * a->ckpt_every);
+    if (a->energy_out && a->energy_every > 0) e = std::min(e, (int)cdiv(n, a->energy_every) * a->energy_every);
+    return e - n;
 }
 }  // namespace
 
@@ -1760,21 +1855,27 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
     if (a->n_rcv > 0 && (!a->rcv_node || !a->traces)) return set_err(p, RBFFD_EINVAL, "receivers need nodes and traces");
     if (a->ckpt && a->ckpt_every <= 0) return set_err(p, RBFFD_EINVAL, "ckpt_every must be positive");
     if (a->energy_out && a->energy_every < 0) return set_err(p, RBFFD_EINVAL, "energy_every < 0");
-    const int64_t eb = p->E.N * p->FE * (int64_t)field_elem_bytes(p->p.fdtype);
-    const int64_t hb = p->H.N * p->FH * (int64_t)field_elem_bytes(p->p.fdtype);
     RunWS w = run_ws(ws);
-    hipLaunchKernelGGL(k_ctr_set, dim3(1), dim3(64), 0, st, w.ctr, 0);
-    int s = 0;
-    if (a->use_graph) {
-        rc = replay_steps(
-            p, a->T, f->cur, st, [&](int c, hipStream_t cs) { full_step(p, f, c, a, w, cs); }, &s);
-        if (rc) return rc;
-    }
+    const bool graphs = a->use_graph && a->n_src <= 0 && a->n_rcv <= 0;
     int c = f->cur;
-    if (s > 0 && (s % 2)) c = 1 - c;
-    for (; s < a->T; ++s) {
-        full_step(p, f, c, a, w, st);
+    for (int n = 0; n < a->T;) {
+        const int plain = graphs ? plain_steps(a, n) : 0;
+        if (plain >= RBFFD_GRAPH_MIN_STEPS) {
+            int done = 0;
+            rc = replay_steps(
+                p, plain, c, st,
+                [&](int b, hipStream_t cs) {
+                    half(p, true, f->E[b], f->H[b], f->H[1 - b], nullptr, cs);
+                    half(p, false, f->E[b], f->H[1 - b], f->E[1 - b], f->eps_r, cs);
+                },
+                &done);
+            if (rc) return rc;
+            n += done;   // even: the buffers are back at c
+            if (done > 0) continue;
+        }
+        full_step(p, f, c, n, a, w, st);
         c = 1 - c;
+        ++n;
     }
     f->cur = (a->T % 2) ? 1 - f->cur : f->cur;
     HIPCHK(p, hipGetLastError());
@@ -1797,7 +1898,7 @@ extern "C" int rbffd_energy(const rbffd_plan* p, const void* E, const void* Ha, 
     if (!p->ready) return set_err(p, RBFFD_ESTATE, "rbffd_weights has not run");
     if (p->K > 1) return set_err(p, RBFFD_ENOTSUP, "energy of a K-field batch: use rbffd_compare per field");
     RunWS w = run_ws(ws);
-    energy(p, E, Ha, Hb, out, w, nullptr, 1, (hipStream_t)stream);
+    energy(p, E, Ha, Hb, out, w, (hipStream_t)stream);
     HIPCHK(p, hipGetLastError());
     return RBFFD_OK;
 }
@@ -1856,7 +1957,7 @@ extern "C" int rbffd_energy_static(const rbffd_plan* p, const void* E, const voi
     if (rc) return rc;
     RunWS w{};
     w.part = parts;
-    energy(p, E, Ha, Hb, out, w, nullptr, 1, st);
+    energy(p, E, Ha, Hb, out, w, st);
     HIPCHK(p, hipGetLastError());
     return RBFFD_OK;
 }
