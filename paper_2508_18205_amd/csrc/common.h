@@ -21,6 +21,9 @@
 #define RBFFD_LDS_BUDGET_3D 131072 // 3D: both operands together up to this size (one
                                    // workgroup per CU; the tuner also tries one operand
                                    // at a time, two per CU)
+#define RBFFD_SMALL 65536         // node counts up to which single-field plans do not
+#define RBFFD_SMALL_2D 80000      // start on the staged kernels (plan.hip)
+#define RBFFD_SMALL_3D_F32 24576
 #define RBFFD_KSLICE 16           // widest field slice of the staged K-field batch
 #define RBFFD_LDS_BUDGET_BATCH 122880
 #define RBFFD_LDS_CU 163840       // LDS of one CU (gfx950)
@@ -101,7 +104,7 @@ struct Variant {
     int block = 256;      // threads per workgroup (multiple of 64)
     int xcd = 1;          // XCD-aware block remap
     int persist = 8;      // K-field batch: resident workgroups per CU
-    int lds = 1;          // use the LDS-staged step kernels when available
+    int lds = 1;          // 0 global gathers, 1 LDS-staged, 2 see rbffd_get_variant, 3 small sets
 };
 
 struct rbffd_plan {

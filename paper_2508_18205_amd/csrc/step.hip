@@ -28,37 +28,44 @@
 
 namespace {
 
+// Kernel arguments are read by cache line, each first touch waited for, so
+// what every kernel needs at its start comes first and what few need last.
 template <typename TS, typename TW>
 struct SA {
+    static constexpr bool kAux = false;
     const TS* E;          // E^n
     const TS* H;          // H update: H^n ; E update: H^{n+1}
-    TS* out;              // H^{n+1} or E^{n+1}
+    const int32_t* hoff;  // LDS staging: halo lists
+    const int32_t* hpool;
+    const uint4* lidx;    // LDS staging: [tiles][Q8][64] x 8 u16 halo positions
     const int4* idx;      // collocated: union chunks ; two-set: curl chunks
-    const int4* idx_h;    // two-set: hv chunks
-    const int32_t* pref;  // two-set: curl reference node
     const TW* wc;
     const TW* wh;
     int64_t N, tiles;
-    int C4, V4, S4;
+    TS* out;              // H^{n+1} or E^{n+1}
+    int C4, V4, S4, Q8, hmax;
     int xcd;
-    double a;             // H update: dt / mu0 ; E update: dt / eps0
-    double g;             // gamma
-    double dt, eps0;
-    const void* eps_r;    // per-node eps_r (double for FP64 fields, else float) or null
-    const uint8_t* emask;
-    const double* wnrm;   // [N][dim] unit wall normals (TEz and 3D curved walls; emask bit 3)
     // TEz: the 2D kernels with the fields' roles exchanged.  te = 1: the
     // vector kernel updates (Ex, Ey) from Hz with factor -kappa_i and the wall
     // mask; nomask = 1: the scalar kernel updates Hz (no wall mask)
     int te, nomask;
-    // LDS staging
-    const uint4* lidx;    // [tiles][Q8][64] x 8 u16 halo positions
-    const int32_t* hpool;
-    const int32_t* hoff;
-    int Q8, hmax;
-    // a run's receivers and soft sources, folded into the half-step kernels:
-    // the H update also records E^n at the receivers, the E update adds the
-    // sources' terms of its step
+    double a;             // H update: dt / mu0 ; E update: dt / eps0
+    double g;             // gamma
+    const void* eps_r;    // per-node eps_r (double for FP64 fields, else float) or null
+    const uint8_t* emask;
+    const int4* idx_h;    // two-set: hv chunks
+    const int32_t* pref;  // two-set: curl reference node
+    double dt, eps0;
+    const double* wnrm;   // [N][dim] unit wall normals (TEz and 3D curved walls; emask bit 3)
+};
+
+// a run's receivers and soft sources, folded into the half-step kernels: the H
+// update also records E^n at the n_rcv receivers, the E update adds the terms
+// of n_src sources.  Steps without them take the kernels without them (looking
+// for none cost the staged kernels 0.2 us each).
+template <typename TS, typename TW>
+struct SX : SA<TS, TW> {
+    static constexpr bool kAux = true;
     int n_rcv, n_src, FE, comp;
     const int32_t* rcv;
     void* trace;          // [n_rcv] row of the traces (TC)
@@ -67,48 +74,58 @@ struct SA {
     const void* swave;
 };
 
-// Receivers: the H update of step n + 1 reads E^{n+1} anyway, so its first
-// n_rcv threads write the trace row of step n (a kernel of its own per step
-// took 3.6 us on the 40k-node dispersion set, 200 receivers).
-template <typename TS, typename TW>
-__device__ __forceinline__ void record_receivers(const SA<TS, TW>& a) {
-    using TC = typename Store<TS>::C;
-    for (int r = (int)(blockIdx.x * blockDim.x + threadIdx.x); r < a.n_rcv; r += (int)(gridDim.x * blockDim.x))
-        ((TC*)a.trace)[r] = Store<TS>::ld1(a.E, (int64_t)a.rcv[r] * a.FE + a.comp);
+// Receivers: the H update of step n + 1 reads E^{n+1} anyway, so the lanes of
+// its tiles (g: tile * 64 + lane) also write the trace row of step n, at their
+// end (a kernel of its own per step took 3.6 us on the 40k-node dispersion set,
+// 200 receivers; done first, it held every load back by 0.4 us).
+template <typename TS, typename TW, typename A>
+__device__ __forceinline__ void record_receivers(const A& a, int64_t g) {
+    if constexpr (A::kAux) {
+        using TC = typename Store<TS>::C;
+        for (int64_t r = g; r < a.n_rcv; r += a.tiles * RBFFD_TILE)
+            ((TC*)a.trace)[r] = Store<TS>::ld1(a.E, (int64_t)a.rcv[r] * a.FE + a.comp);
+    }
 }
 
 // Soft sources: E at node i after the bracket gains amp * wave for every
 // source on it, in source order, each sum rounded to the storage type as a
 // store would; PEC nodes stay 0.
-template <typename TS, typename TW>
-__device__ __forceinline__ typename Store<TS>::C sourced(const SA<TS, TW>& a, int64_t i, bool free_,
-                                                         typename Store<TS>::C v) {
+template <typename TS, typename TW, typename A>
+__device__ __forceinline__ typename Store<TS>::C sourced(const A& a, int64_t i, bool free_, typename Store<TS>::C v) {
     using TC = typename Store<TS>::C;
     if (!free_) return (TC)0;
-    for (int s = 0; s < a.n_src; ++s)
-        if (a.src[s] == (int32_t)i)
-            v = Store<TS>::rnd(Store<TS>::rnd(v) + ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s]);
+    if constexpr (A::kAux)
+        for (int s = 0; s < a.n_src; ++s)
+            if (a.src[s] == (int32_t)i)
+                v = Store<TS>::rnd(Store<TS>::rnd(v) + ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s]);
     return v;
 }
 // 3D: the source acts on Ez; on a curved wall (mask bit 3) E is already
 // projected on the normal n, so adding v n_z n keeps (E + v e_z) projected
-template <typename TS, typename TW>
-__device__ __forceinline__ void sourced3(const SA<TS, TW>& a, int64_t i, uint8_t m, typename Store<TS>::C& x,
+template <typename TS, typename TW, typename A>
+__device__ __forceinline__ void sourced3(const A& a, int64_t i, uint8_t m, typename Store<TS>::C& x,
                                          typename Store<TS>::C& y, typename Store<TS>::C& z) {
     using S = Store<TS>;
     using TC = typename S::C;
-    for (int s = 0; s < a.n_src; ++s) {
-        if (a.src[s] != (int32_t)i) continue;
-        const TC v = ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s];
-        if (m & 8) {
-            const double* n = a.wnrm + 3 * i;
-            x = S::rnd(S::rnd(x) + v * (TC)n[2] * (TC)n[0]);
-            y = S::rnd(S::rnd(y) + v * (TC)n[2] * (TC)n[1]);
-            z = S::rnd(S::rnd(z) + v * (TC)n[2] * (TC)n[2]);
-        } else {
-            z = (m & 4) ? S::rnd(S::rnd(z) + v) : (TC)0;
+    if constexpr (A::kAux)
+        for (int s = 0; s < a.n_src; ++s) {
+            if (a.src[s] != (int32_t)i) continue;
+            const TC v = ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s];
+            if (m & 8) {
+                const double* n = a.wnrm + 3 * i;
+                x = S::rnd(S::rnd(x) + v * (TC)n[2] * (TC)n[0]);
+                y = S::rnd(S::rnd(y) + v * (TC)n[2] * (TC)n[1]);
+                z = S::rnd(S::rnd(z) + v * (TC)n[2] * (TC)n[2]);
+            } else {
+                z = (m & 4) ? S::rnd(S::rnd(z) + v) : (TC)0;
+            }
         }
-    }
+}
+
+template <typename TC>
+__device__ __forceinline__ TC* lds_base() {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    return reinterpret_cast<TC*>(smem_raw);
 }
 
 // PEC on the in-plane E of the TEz polarisation: bit 0 / 1 of the mask keeps
@@ -160,9 +177,8 @@ __device__ __forceinline__ typename Store<TS>::C kappa_of(const SA<TS, TW>& a, i
 }
 
 // ---- 2D TMz, collocated ----------------------------------------------------
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_h2(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_h2(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -222,25 +238,26 @@ __global__ __launch_bounds__(512) void k_h2(SA<TS, TW> a) {
             vy += (TC)wh[u] * (hy - hy0);
         }
     }
+    record_receivers<TS, TW>(a, i);
     if (i < a.N) {
         const TC G = (TC)a.g;
         if (!a.te) {
-            const TC A = (TC)a.a;
-            S::st2(a.out, i, hx0 + A * (-dy + G * vx), hy0 + A * (dx + G * vy));
+            const TC F = (TC)a.a;
+            S::st2(a.out, i, hx0 + F * (-dy + G * vx), hy0 + F * (dx + G * vy));
         } else {
             // TEz (Ex, Ey) <- E + kappa (D^dy Hz + gamma HV, -D^dx Hz + gamma HV),
             // written as E - kappa (-D^dy Hz - gamma HV, D^dx Hz - gamma HV) with
             // the host's gamma negated; then the wall mask
-            const TC A = -kappa_of(a, i);
-            TC ex = hx0 + A * (-dy + G * vx), ey = hy0 + A * (dx + G * vy);
+            const TC F = -kappa_of(a, i);
+            TC ex = hx0 + F * (-dy + G * vx), ey = hy0 + F * (dx + G * vy);
             te_wall(a.emask[i], a.wnrm, i, ex, ey);
             S::st2(a.out, i, ex, ey);
         }
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_e2(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_e2(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -294,7 +311,7 @@ __global__ __launch_bounds__(512) void k_e2(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
+        const TC v = sourced<TS, TW>(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
@@ -302,9 +319,8 @@ __global__ __launch_bounds__(512) void k_e2(SA<TS, TW> a) {
 // ---- 2D TMz, two node sets ---------------------------------------------------
 // H update: curl of E from the E set (reference = nearest E node), HV of H on
 // the H set.  E update: curl of H from the H set, HV of E on the E set.
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_h2x(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_h2x(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -344,25 +360,26 @@ __global__ __launch_bounds__(512) void k_h2x(SA<TS, TW> a) {
             vy += (TC)wh[u] * (hy - hy0);
         }
     }
+    record_receivers<TS, TW>(a, i);
     if (i < a.N) {
         const TC G = (TC)a.g;
         if (!a.te) {
-            const TC A = (TC)a.a;
-            S::st2(a.out, i, hx0 + A * (-dy + G * vx), hy0 + A * (dx + G * vy));
+            const TC F = (TC)a.a;
+            S::st2(a.out, i, hx0 + F * (-dy + G * vx), hy0 + F * (dx + G * vy));
         } else {
             // TEz (Ex, Ey) <- E + kappa (D^dy Hz + gamma HV, -D^dx Hz + gamma HV),
             // written as E - kappa (-D^dy Hz - gamma HV, D^dx Hz - gamma HV) with
             // the host's gamma negated; then the wall mask
-            const TC A = -kappa_of(a, i);
-            TC ex = hx0 + A * (-dy + G * vx), ey = hy0 + A * (dx + G * vy);
+            const TC F = -kappa_of(a, i);
+            TC ex = hx0 + F * (-dy + G * vx), ey = hy0 + F * (dx + G * vy);
             te_wall(a.emask[i], a.wnrm, i, ex, ey);
             S::st2(a.out, i, ex, ey);
         }
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_e2x(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_e2x(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -399,7 +416,7 @@ __global__ __launch_bounds__(512) void k_e2x(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
+        const TC v = sourced<TS, TW>(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
@@ -409,9 +426,8 @@ __global__ __launch_bounds__(512) void k_e2x(SA<TS, TW> a) {
 // each sum every fourth curl chunk and every fourth hyperviscosity chunk, and
 // the partial sums meet in LDS in a fixed order (the small-set scheme of
 // k_h2s / k_e2s below, for the staggered variant).
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_h2xs(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_h2xs(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     __shared__ TC part[3][4][RBFFD_TILE];
@@ -458,6 +474,7 @@ __global__ __launch_bounds__(256) void k_h2xs(SA<TS, TW> a) {
         part[r - 1][3][lane] = vy;
     }
     __syncthreads();
+    if (r == 0) record_receivers<TS, TW>(a, i);
     if (r > 0 || i >= a.N) return;
     dx = ((dx + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     dy = ((dy + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
@@ -465,18 +482,18 @@ __global__ __launch_bounds__(256) void k_h2xs(SA<TS, TW> a) {
     vy = ((vy + part[0][3][lane]) + part[1][3][lane]) + part[2][3][lane];
     const TC G = (TC)a.g;
     if (!a.te) {
-        const TC A = (TC)a.a;
-        S::st2(a.out, i, hx0 + A * (-dy + G * vx), hy0 + A * (dx + G * vy));
+        const TC F = (TC)a.a;
+        S::st2(a.out, i, hx0 + F * (-dy + G * vx), hy0 + F * (dx + G * vy));
     } else {
-        const TC A = -kappa_of(a, i);
-        TC ex = hx0 + A * (-dy + G * vx), ey = hy0 + A * (dx + G * vy);
+        const TC F = -kappa_of(a, i);
+        TC ex = hx0 + F * (-dy + G * vx), ey = hy0 + F * (dx + G * vy);
         te_wall(a.emask[i], a.wnrm, i, ex, ey);
         S::st2(a.out, i, ex, ey);
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_e2xs(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_e2xs(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     __shared__ TC part[3][2][RBFFD_TILE];
@@ -520,7 +537,7 @@ __global__ __launch_bounds__(256) void k_e2xs(SA<TS, TW> a) {
     cu = ((cu + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     ve = ((ve + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
     const TC k = kappa_of(a, i);
-    const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
+    const TC v = sourced<TS, TW>(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
     S::st1(a.out, i, v);
 }
 
@@ -531,9 +548,8 @@ __global__ __launch_bounds__(256) void k_e2xs(SA<TS, TW> a) {
 // of dependent loads per node is four times shorter, for launches too small
 // to fill the chip.  Same terms as k_h2 / k_e2; only the order of the partial
 // sums differs.
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_h2s(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_h2s(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -582,6 +598,7 @@ __global__ __launch_bounds__(256) void k_h2s(SA<TS, TW> a) {
         part[r - 1][3][lane] = vy;
     }
     __syncthreads();
+    if (r == 0) record_receivers<TS, TW>(a, i);
     if (r > 0 || i >= a.N) return;
     dx = ((dx + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     dy = ((dy + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
@@ -589,18 +606,18 @@ __global__ __launch_bounds__(256) void k_h2s(SA<TS, TW> a) {
     vy = ((vy + part[0][3][lane]) + part[1][3][lane]) + part[2][3][lane];
     const TC G = (TC)a.g;
     if (!a.te) {
-        const TC A = (TC)a.a;
-        S::st2(a.out, i, hx0 + A * (-dy + G * vx), hy0 + A * (dx + G * vy));
+        const TC F = (TC)a.a;
+        S::st2(a.out, i, hx0 + F * (-dy + G * vx), hy0 + F * (dx + G * vy));
     } else {
-        const TC A = -kappa_of(a, i);
-        TC ex = hx0 + A * (-dy + G * vx), ey = hy0 + A * (dx + G * vy);
+        const TC F = -kappa_of(a, i);
+        TC ex = hx0 + F * (-dy + G * vx), ey = hy0 + F * (dx + G * vy);
         te_wall(a.emask[i], a.wnrm, i, ex, ey);
         S::st2(a.out, i, ex, ey);
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_e2s(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_e2s(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -646,14 +663,13 @@ __global__ __launch_bounds__(256) void k_e2s(SA<TS, TW> a) {
     cu = ((cu + part[0][0][lane]) + part[1][0][lane]) + part[2][0][lane];
     ve = ((ve + part[0][1][lane]) + part[1][1][lane]) + part[2][1][lane];
     const TC k = kappa_of(a, i);
-    const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
+    const TC v = sourced<TS, TW>(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
     S::st1(a.out, i, v);
 }
 
 // ---- 3D, collocated: E and H stored as (x, y, z, pad) -------------------------
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_h3(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_h3(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -722,16 +738,17 @@ __global__ __launch_bounds__(512) void k_h3(SA<TS, TW> a) {
             vz += (TC)wh[u] * (hz - hz0);
         }
     }
+    record_receivers<TS, TW>(a, i);
     if (i < a.N) {
-        const TC A = (TC)a.a, G = (TC)a.g;
+        const TC F = (TC)a.a, G = (TC)a.g;
         // H <- H - a (curl E - gamma D^hv H)
-        S::st3(a.out, i, hx0 - A * ((yEz - zEy) - G * vx), hy0 - A * ((zEx - xEz) - G * vy),
-               hz0 - A * ((xEy - yEx) - G * vz));
+        S::st3(a.out, i, hx0 - F * ((yEz - zEy) - G * vx), hy0 - F * ((zEx - xEz) - G * vy),
+               hz0 - F * ((xEy - yEx) - G * vz));
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(512) void k_e3(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(512) void k_e3(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     const int64_t tile = tile_of(a);
@@ -806,9 +823,213 @@ __global__ __launch_bounds__(512) void k_e3(SA<TS, TW> a) {
         TC nz = ez0 + k * ((xHy - yHx) + G * vz);
         const uint8_t m = a.emask[i];
         wall3(m, a.wnrm, i, nx, ny, nz);
-        sourced3(a, i, m, nx, ny, nz);
+        sourced3<TS, TW>(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
+}
+
+// ---- 3D, small node sets ------------------------------------------------------
+// As k_h2s / k_e2s with eight wavefronts per 64-node tile: launches too small to
+// fill the chip are bound by the chain of dependent loads (stencil indices, then
+// the values they name), so the tile's slot chunks are dealt out to the
+// wavefronts, curl chunks first, and a wavefront requests the indices of the
+// chunks it holds, then all they name, before it uses any.  The staged kernels
+// take 45 us per step on a 13.5k-node box (27 or 14 workgroups on 256 CUs),
+// these 15.0 in FP64 and 14.4 in FP32.
+constexpr int kSplit3 = 8;
+
+// curl sums (x, y, z of the field C) and hyperviscosity sums (of the field V)
+// of the tile's nodes, complete in every lane of wavefront 0.
+//
+// FP64: a wavefront multiplies its chunks by their weights, and the partial
+// sums meet in LDS, the first six wavefronts each adding up one of the six.
+// One chunk at a time: two spill (46.8 against 26.6 us per step, 30k nodes);
+// sixteen wavefronts per tile, 53.7 against 47.9 us at 64k nodes.
+template <typename TS, typename TW>
+__device__ __forceinline__ void small_sums3(const SA<TS, TW>& a, const TS* C, const TS* V, int64_t tile, int r, int lane,
+                                            const double (&c0)[3], const double (&v0)[3], double (&sum)[6]) {
+    using S = Store<TS>;
+    __shared__ double part[kSplit3][6][RBFFD_TILE];
+    const int4* pi = a.idx + tile * a.S4 * RBFFD_TILE + lane;
+    const TW* pc = a.wc + tile * a.C4 * 3 * WF<TW>::CH + lane * WF<TW>::LS;
+    const TW* ph = a.wh + tile * a.V4 * WF<TW>::CH + lane * WF<TW>::LS;
+    const int total = a.C4 + a.V4;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sum[k] = 0;
+    for (int g = r; g < total; g += kSplit3) {
+        double f[3];
+        if (g < a.C4) {
+            const int4 j = pi[g * RBFFD_TILE];
+            TW w[3][4];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ldw4p(pc + (g * 3 + k) * WF<TW>::CH, w[k]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                S::ld3(C, idx4(j, u), f[0], f[1], f[2]);
+                const double x = f[0] - c0[0], y = f[1] - c0[1], z = f[2] - c0[2];
+                sum[0] += w[1][u] * z - w[2][u] * y;
+                sum[1] += w[2][u] * x - w[0][u] * z;
+                sum[2] += w[0][u] * y - w[1][u] * x;
+            }
+        } else {
+            const int4 j = pi[(g - a.C4) * RBFFD_TILE];
+            TW w[4];
+            ldw4p(ph + (g - a.C4) * WF<TW>::CH, w);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                S::ld3(V, idx4(j, u), f[0], f[1], f[2]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sum[3 + k] += w[u] * (f[k] - v0[k]);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) part[r][k][lane] = sum[k];
+    __syncthreads();
+    if (r < 6) {
+        double v = part[0][r][lane];
+#pragma unroll
+        for (int q = 1; q < kSplit3; ++q) v += part[q][r][lane];
+        part[0][r][lane] = v;   // read and written by this wavefront only
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sum[k] = part[0][k][lane];
+}
+
+// FP32: the wavefronts only fetch, into LDS ([slot][component][lane]); six of
+// them then each sum one or two of the nine sums over all slots, in slot order
+// and in the arithmetic of the staged kernels, so that FP32 results do not
+// depend on which of the two runs.  Their weights, nine chunks at a time in
+// registers, are requested before the values.  A tile of n = 35, n_hv = 71 takes
+// 83 KB of LDS, so a CU holds one workgroup; keeping only the slots in use (80
+// KB, two per CU) needs a test per slot: 16.3 against 14.4 us per step at 13.5k
+// nodes.
+constexpr int kAhead3 = 9;
+inline size_t small3_lds(const OpBlock& o) { return (size_t)(o.C4 + o.V4) * 4 * 3 * RBFFD_TILE * sizeof(float); }
+template <typename TS, typename TW>
+__device__ __forceinline__ void small_sums3(const SA<TS, TW>& a, const TS* C, const TS* V, int64_t tile, int r, int lane,
+                                            const float (&c0)[3], const float (&v0)[3], float (&sum)[6]) {
+    using S = Store<TS>;
+    float* sv = lds_base<float>() + lane;
+    const int4* pi = a.idx + tile * a.S4 * RBFFD_TILE + lane;
+    const int total = a.C4 + a.V4;
+    // wavefronts 0..2 sum the curl products of the x, y, z weights, 3..5 the
+    // hyperviscosity of component r - 3
+    const bool curl = r < 3;
+    const int n4 = r < 6 ? (curl ? a.C4 : a.V4) : 0;
+    const TW* pw = curl ? a.wc + (tile * a.C4 * 3 + r) * WF<TW>::CH + lane * WF<TW>::LS
+                        : a.wh + tile * a.V4 * WF<TW>::CH + lane * WF<TW>::LS;
+    const int64_t ws = (curl ? 3 : 1) * WF<TW>::CH;
+    TW w[kAhead3][4];
+#pragma unroll
+    for (int i = 0; i < kAhead3; ++i)
+        if (i < n4) ldw4p(pw + i * ws, w[i]);
+    for (int g0 = r; g0 < total; g0 += 2 * kSplit3) {
+        int4 j[2];
+        float f[2][4][3];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int g = g0 + kSplit3 * t;
+            if (g < total) j[t] = pi[(g < a.C4 ? g : g - a.C4) * RBFFD_TILE];
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int g = g0 + kSplit3 * t;
+            if (g >= total) continue;
+            const TS* F = g < a.C4 ? C : V;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) S::ld3(F, idx4(j[t], u), f[t][u][0], f[t][u][1], f[t][u][2]);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int g = g0 + kSplit3 * t;
+            if (g >= total) continue;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    sv[((g * 4 + u) * 3 + k) * RBFFD_TILE] = f[t][u][k] - (g < a.C4 ? c0[k] : v0[k]);
+        }
+    }
+    __syncthreads();
+    // components that the x, y, z weights multiply: (y, z), (x, z), (x, y)
+    const int kp = r == 0 ? 1 : 0, kq = r == 2 ? 1 : 2;
+    float p = 0, q = 0;
+    for (int b = 0; b < n4; b += kAhead3) {
+#pragma unroll
+        for (int i = 0; i < kAhead3; ++i) {
+            if (b + i >= n4) break;
+            const float* s = sv + (curl ? b + i : a.C4 + b + i) * 12 * RBFFD_TILE;
+            if (curl) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    p += (float)w[i][u] * s[(u * 3 + kp) * RBFFD_TILE];
+                    q += (float)w[i][u] * s[(u * 3 + kq) * RBFFD_TILE];
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) p += (float)w[i][u] * s[(u * 3 + r - 3) * RBFFD_TILE];
+            }
+            if (b + i + kAhead3 < n4) ldw4p(pw + (b + i + kAhead3) * ws, w[i]);
+        }
+    }
+    __syncthreads();   // the sums take the place of the values
+    if (curl) {
+        sv[(2 * r) * RBFFD_TILE] = p;
+        sv[(2 * r + 1) * RBFFD_TILE] = q;
+    } else if (r < 6) {
+        sv[(3 + r) * RBFFD_TILE] = p;
+    }
+    __syncthreads();
+    // (x f_y, x f_z, y f_x, y f_z, z f_x, z f_y), v
+    float c[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) c[k] = sv[k * RBFFD_TILE];
+    sum[0] = c[3] - c[5];
+    sum[1] = c[4] - c[1];
+    sum[2] = c[0] - c[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sum[3 + k] = c[6 + k];
+}
+
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(64 * kSplit3) void k_h3s(A a) {
+    using S = Store<TS>;
+    using TC = typename S::C;
+    const int64_t tile = a.xcd ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t i = tile * RBFFD_TILE + lane;
+    const int64_t ic = i < a.N ? i : a.N - 1;
+    TC e0[3], h0[3], s[6];
+    S::ld3(a.E, ic, e0[0], e0[1], e0[2]);
+    S::ld3(a.H, ic, h0[0], h0[1], h0[2]);
+    small_sums3<TS, TW>(a, a.E, a.H, tile, r, lane, e0, h0, s);
+    if (r == 0) record_receivers<TS, TW>(a, i);
+    if (r > 0 || i >= a.N) return;
+    const TC F = (TC)a.a, G = (TC)a.g;
+    S::st3(a.out, i, h0[0] - F * (s[0] - G * s[3]), h0[1] - F * (s[1] - G * s[4]), h0[2] - F * (s[2] - G * s[5]));
+}
+
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(64 * kSplit3) void k_e3s(A a) {
+    using S = Store<TS>;
+    using TC = typename S::C;
+    const int64_t tile = a.xcd ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t i = tile * RBFFD_TILE + lane;
+    const int64_t ic = i < a.N ? i : a.N - 1;
+    TC e0[3], h0[3], s[6];
+    S::ld3(a.E, ic, e0[0], e0[1], e0[2]);
+    S::ld3(a.H, ic, h0[0], h0[1], h0[2]);
+    small_sums3<TS, TW>(a, a.H, a.E, tile, r, lane, h0, e0, s);
+    if (r > 0 || i >= a.N) return;
+    const TC k = kappa_of(a, i), G = (TC)a.g;
+    TC x = e0[0] + k * (s[0] + G * s[3]), y = e0[1] + k * (s[1] + G * s[4]), z = e0[2] + k * (s[2] + G * s[5]);
+    const uint8_t m = a.emask[i];
+    wall3(m, a.wnrm, i, x, y, z);
+    sourced3<TS, TW>(a, i, m, x, y, z);
+    S::st3(a.out, i, x, y, z);
 }
 
 // ---- LDS-staged variants ------------------------------------------------------
@@ -905,12 +1126,6 @@ __device__ __forceinline__ void st_lds2(double* p, double x, double y) {
     *reinterpret_cast<double2*>(p) = make_double2(x, y);
 }
 
-template <typename TC>
-__device__ __forceinline__ TC* lds_base() {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    return reinterpret_cast<TC*>(smem_raw);
-}
-
 // Halo staging with several loads in flight per thread: each round takes up
 // to SB list entries per thread, loads all their list values, then all their
 // field values, then stores them (a plain loop waits for each load in turn).
@@ -944,9 +1159,8 @@ struct Val6 {
     TC v[6];
 };
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_h2l(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_h2l(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -1011,25 +1225,26 @@ __global__ __launch_bounds__(256) void k_h2l(SA<TS, TW> a) {
             }
         }
     }
+    record_receivers<TS, TW>(a, i);
     if (i < a.N) {
         const TC G = (TC)a.g;
         if (!a.te) {
-            const TC A = (TC)a.a;
-            S::st2(a.out, i, hx0 + A * (-dy + G * vx), hy0 + A * (dx + G * vy));
+            const TC F = (TC)a.a;
+            S::st2(a.out, i, hx0 + F * (-dy + G * vx), hy0 + F * (dx + G * vy));
         } else {
             // TEz (Ex, Ey) <- E + kappa (D^dy Hz + gamma HV, -D^dx Hz + gamma HV),
             // written as E - kappa (-D^dy Hz - gamma HV, D^dx Hz - gamma HV) with
             // the host's gamma negated; then the wall mask
-            const TC A = -kappa_of(a, i);
-            TC ex = hx0 + A * (-dy + G * vx), ey = hy0 + A * (dx + G * vy);
+            const TC F = -kappa_of(a, i);
+            TC ex = hx0 + F * (-dy + G * vx), ey = hy0 + F * (dx + G * vy);
             te_wall(a.emask[i], a.wnrm, i, ex, ey);
             S::st2(a.out, i, ex, ey);
         }
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(256) void k_e2l(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(256) void k_e2l(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     using WV = typename WF<TW>::V;
@@ -1090,14 +1305,13 @@ __global__ __launch_bounds__(256) void k_e2l(SA<TS, TW> a) {
     }
     if (i < a.N) {
         const TC k = kappa_of(a, i);
-        const TC v = sourced(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
+        const TC v = sourced<TS, TW>(a, i, a.nomask || (a.emask[i] & 1), e0 + k * (cu + (TC)a.g * ve));
         S::st1(a.out, i, v);
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3l(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3l(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sE = lds_base<TC>();                           // 3 values per entry
@@ -1167,15 +1381,16 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3l(SA<TS, TW> a) {
             }
         }
     }
+    record_receivers<TS, TW>(a, i);
     if (i < a.N) {
-        const TC A = (TC)a.a, G = (TC)a.g;
-        S::st3(a.out, i, hx0 - A * ((yEz - zEy) - G * vx), hy0 - A * ((zEx - xEz) - G * vy),
-               hz0 - A * ((xEy - yEx) - G * vz));
+        const TC F = (TC)a.a, G = (TC)a.g;
+        S::st3(a.out, i, hx0 - F * ((yEz - zEy) - G * vx), hy0 - F * ((zEx - xEz) - G * vy),
+               hz0 - F * ((xEy - yEx) - G * vz));
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sE = lds_base<TC>();
@@ -1251,7 +1466,7 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(SA<TS, TW> a) {
         TC nz = ez0 + k * ((xHy - yHx) + G * vz);
         const uint8_t m = a.emask[i];
         wall3(m, a.wnrm, i, nx, ny, nz);
-        sourced3(a, i, m, nx, ny, nz);
+        sourced3<TS, TW>(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
 }
@@ -1338,9 +1553,8 @@ __device__ __forceinline__ void hv_sums3(const TC* sF, const uint4* pl, const TW
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3p(SA<TS, TW> a) {
-    record_receivers(a);
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3p(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sF = lds_base<TC>();
@@ -1366,16 +1580,17 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3p(SA<TS, TW> a) {
     stage_vec3<TS>(a.H, a.hpool + h0, hc, sF);
     __syncthreads();
     if (live) hv_sums3<TC, TW>(sF, pl, ph, a.V4, h0v, v);
+    if (live) record_receivers<TS, TW>(a, i);
     if (live && i < a.N) {
-        const TC A = (TC)a.a, G = (TC)a.g;
+        const TC F = (TC)a.a, G = (TC)a.g;
         // c = (xEy, xEz, yEx, yEz, zEx, zEy)
-        S::st3(a.out, i, h0v[0] - A * ((c[3] - c[5]) - G * v[0]), h0v[1] - A * ((c[4] - c[1]) - G * v[1]),
-               h0v[2] - A * ((c[0] - c[2]) - G * v[2]));
+        S::st3(a.out, i, h0v[0] - F * ((c[3] - c[5]) - G * v[0]), h0v[1] - F * ((c[4] - c[1]) - G * v[1]),
+               h0v[2] - F * ((c[0] - c[2]) - G * v[2]));
     }
 }
 
-template <typename TS, typename TW>
-__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(SA<TS, TW> a) {
+template <typename TS, typename TW, typename A>
+__global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sF = lds_base<TC>();
@@ -1409,7 +1624,7 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(SA<TS, TW> a) {
         TC nz = e0[2] + k * ((c[0] - c[2]) + G * v[2]);
         const uint8_t m = a.emask[i];
         wall3(m, a.wnrm, i, nx, ny, nz);
-        sourced3(a, i, m, nx, ny, nz);
+        sourced3<TS, TW>(a, i, m, nx, ny, nz);
         S::st3(a.out, i, nx, ny, nz);
     }
 }
@@ -1581,6 +1796,13 @@ void fill_sa(const rbffd_plan* p, const OpBlock& o, SA<TS, TW>& a, bool hupd) {
     a.hmax = o.hmax;
 }
 
+// whether the plan's variant takes the small-set kernels; a 3D FP32 tile whose
+// values do not fit a CU's LDS takes the staged ones
+bool small_set(const rbffd_plan* p, const OpBlock& o) {
+    if (p->var.lds != 3) return false;
+    return p->dim == 2 || p->p.fdtype == RBFFD_F64 || small3_lds(o) <= RBFFD_LDS_CU;
+}
+
 // what a run folds into one half step (null pointers: nothing)
 struct HalfAux {
     const int32_t* rcv = nullptr;   // H update
@@ -1591,14 +1813,21 @@ struct HalfAux {
     int n_rcv = 0, n_src = 0;
 };
 
+// kernel K with the auxiliaries of a run when this half step has any
+#define RBFFD_LAUNCH_HALF(K, grid, block, lds)                                                              \
+    do {                                                                                                    \
+        if (aux) hipLaunchKernelGGL((K<TS, TW, SX<TS, TW>>), grid, block, lds, st, a);                       \
+        else hipLaunchKernelGGL((K<TS, TW, SA<TS, TW>>), grid, block, lds, st, (const SA<TS, TW>&)a);        \
+    } while (0)
+
 template <typename TS, typename TW>
 void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r,
                  const HalfAux& x, hipStream_t st) {
     // compressed (W22) weights exist only for the 2D collocated kernels
     constexpr bool kW22 = std::is_same<TW, w22>::value;
     const OpBlock& o = hupd ? p->opH : p->opE;
-    SA<TS, TW> a{};
-    fill_sa(p, o, a, hupd);
+    SX<TS, TW> a{};
+    fill_sa<TS, TW>(p, o, a, hupd);
     a.E = (const TS*)E;
     a.H = (const TS*)H;
     a.out = (TS*)out;
@@ -1612,6 +1841,7 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
     a.src = x.src;
     a.samp = x.samp;
     a.swave = x.swave;
+    const bool aux = (hupd ? x.n_rcv : x.n_src) > 0;
     if (p->p.pol == RBFFD_POL_TE) {
         // TEz: the Hz update runs the scalar (E-update) kernel on (Hz, E) and
         // the E update the vector (H-update) kernel on (Hz_new, E); the
@@ -1624,13 +1854,32 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
         a.te = hupd ? 0 : 1;
         hupd = !hupd;
     }
-    if (p->collocated && o.hmax > 0 && p->var.lds && !(p->var.lds == 3 && p->dim == 2)) {
+    if (small_set(p, o)) {
+        const dim3 grid((unsigned)o.tiles), block(p->dim == 2 ? 256 : 64 * kSplit3);
+        if (p->dim == 2 && p->collocated) {
+            if (hupd) RBFFD_LAUNCH_HALF(k_h2s, grid, block, 0);
+            else RBFFD_LAUNCH_HALF(k_e2s, grid, block, 0);
+            return;
+        }
+        if constexpr (!kW22) {   // compressed weights: 2D collocated plans only
+            if (p->dim == 2) {
+                if (hupd) RBFFD_LAUNCH_HALF(k_h2xs, grid, block, 0);
+                else RBFFD_LAUNCH_HALF(k_e2xs, grid, block, 0);
+            } else {
+                const size_t lds = std::is_same<TS, double>::value ? 0 : small3_lds(o);
+                if (hupd) RBFFD_LAUNCH_HALF(k_h3s, grid, block, lds);
+                else RBFFD_LAUNCH_HALF(k_e3s, grid, block, lds);
+            }
+        }
+        return;
+    }
+    if (p->collocated && o.hmax > 0 && p->var.lds) {
         using TC = typename Store<TS>::C;
         const dim3 grid((unsigned)o.nwg), block(o.wgt);
         if (p->dim == 2) {
             const size_t lds = (size_t)(((o.hmax + 3) & ~3) + 2 * o.hmax) * sizeof(TC);
-            if (hupd) hipLaunchKernelGGL((k_h2l<TS, TW>), grid, block, lds, st, a);
-            else hipLaunchKernelGGL((k_e2l<TS, TW>), grid, block, lds, st, a);
+            if (hupd) RBFFD_LAUNCH_HALF(k_h2l, grid, block, lds);
+            else RBFFD_LAUNCH_HALF(k_e2l, grid, block, lds);
             return;
         }
         if constexpr (kW22) {
@@ -1638,44 +1887,34 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
             return;
         } else if (o.stage == 1 && p->var.lds != 2) {
             const size_t lds = (size_t)6 * o.hmax * sizeof(TC);
-            if (hupd) hipLaunchKernelGGL((k_h3l<TS, TW>), grid, block, lds, st, a);
-            else hipLaunchKernelGGL((k_e3l<TS, TW>), grid, block, lds, st, a);
+            if (hupd) RBFFD_LAUNCH_HALF(k_h3l, grid, block, lds);
+            else RBFFD_LAUNCH_HALF(k_e3l, grid, block, lds);
         } else {
             const size_t lds = (size_t)3 * o.hmax * sizeof(TC);
-            if (hupd) hipLaunchKernelGGL((k_h3p<TS, TW>), grid, block, lds, st, a);
-            else hipLaunchKernelGGL((k_e3p<TS, TW>), grid, block, lds, st, a);
+            if (hupd) RBFFD_LAUNCH_HALF(k_h3p, grid, block, lds);
+            else RBFFD_LAUNCH_HALF(k_e3p, grid, block, lds);
         }
-        return;
-    }
-    if (p->var.lds == 3 && p->dim == 2 && p->collocated) {
-        const dim3 grid((unsigned)o.tiles), block(256);
-        if (hupd) hipLaunchKernelGGL((k_h2s<TS, TW>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((k_e2s<TS, TW>), grid, block, 0, st, a);
         return;
     }
     const int wpb = p->var.block / 64;
     const dim3 grid((unsigned)cdiv(o.tiles, wpb)), block(p->var.block);
     if (p->dim == 2 && p->collocated) {
-        if (hupd) hipLaunchKernelGGL((k_h2<TS, TW>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((k_e2<TS, TW>), grid, block, 0, st, a);
+        if (hupd) RBFFD_LAUNCH_HALF(k_h2, grid, block, 0);
+        else RBFFD_LAUNCH_HALF(k_e2, grid, block, 0);
         return;
     }
     if constexpr (!kW22) {
-        if (p->dim == 2 && p->var.lds == 3) {
-            const dim3 g1((unsigned)o.tiles), b1(256);
-            if (hupd) hipLaunchKernelGGL((k_h2xs<TS, TW>), g1, b1, 0, st, a);
-            else hipLaunchKernelGGL((k_e2xs<TS, TW>), g1, b1, 0, st, a);
-            return;
-        }
         if (p->dim == 2) {
-            if (hupd) hipLaunchKernelGGL((k_h2x<TS, TW>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((k_e2x<TS, TW>), grid, block, 0, st, a);
+            if (hupd) RBFFD_LAUNCH_HALF(k_h2x, grid, block, 0);
+            else RBFFD_LAUNCH_HALF(k_e2x, grid, block, 0);
         } else {
-            if (hupd) hipLaunchKernelGGL((k_h3<TS, TW>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((k_e3<TS, TW>), grid, block, 0, st, a);
+            if (hupd) RBFFD_LAUNCH_HALF(k_h3, grid, block, 0);
+            else RBFFD_LAUNCH_HALF(k_e3, grid, block, 0);
         }
     }
 }
+
+#undef RBFFD_LAUNCH_HALF
 
 void half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r, hipStream_t st,
           const HalfAux& x = HalfAux()) {
@@ -2030,8 +2269,8 @@ extern "C" int rbffd_autotune(rbffd_plan* p, rbffd_fields* f, int32_t reps, void
             if (p->dim == 3 && p->opH.stage == 1) cand.push_back(Variant{256, 1, 8, 2});
         }
     }
-    if (p->K == 1 && p->dim == 2) {
-        // four wavefronts per 64-node tile (small node sets), collocated or two sets
+    if (p->K == 1) {
+        // several wavefronts per 64-node tile (small node sets)
         for (int x : {0, 1}) cand.push_back(Variant{256, x, 8, 3});
     }
     Variant best = p->var;
