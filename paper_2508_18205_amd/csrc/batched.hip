@@ -875,7 +875,7 @@ int batched_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_args* a, v
     for (int n = 0; n < a->T;) {
         // plain steps up to the next energy sample (or the end)
         const int plain = (eo ? std::min<int64_t>(a->T, cdiv(n, a->energy_every) * a->energy_every) : a->T) - n;
-        if (a->use_graph && plain >= RBFFD_GRAPH_MIN_STEPS) {
+        if (a->use_graph && plain >= RBFFD_GRAPH_MIN_STEPS && p->opE.tiles <= RBFFD_GRAPH_TILES) {
             int done = 0;
             const int rc = replay_steps(
                 p, plain, f->cur, st, [&](int c, hipStream_t cs) { full_step_b(p, f, c, nullptr, nullptr, cs); }, &done);

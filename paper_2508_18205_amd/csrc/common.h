@@ -192,41 +192,38 @@ int64_t setup_ws_bytes(const rbffd_plan* p);
 int capture_stream(const rbffd_plan* p, hipStream_t* out);
 
 // ---- HIP-graph step loop -----------------------------------------------------
-// Long stretches of plain steps (no sample, checkpoint, source or receiver in
-// them) are replayed from HIP graphs: one graph of S captured steps (S even,
-// at most RBFFD_GRAPH_STEPS) replayed T / S times, then one graph of the
-// remaining whole step pairs.  Shorter stretches are launched one by one:
-// capturing and instantiating a graph costs about 0.8 ms, and a replayed step
-// of the smallest node sets (51^2, two 3.7 us kernels) takes 7.2 us against
-// 8.2 us launched, so a graph pays from about 500 steps on.  rec(c, stream) records
-// one full step reading buffer set c; the buffers alternate within a graph
-// and, S being even, every replay leaves them as it found them.  *done
-// receives the number of steps replayed (even); the caller runs the rest.
+// Stretches of plain steps (no sample, checkpoint, source or receiver in them)
+// are replayed from a HIP graph of RBFFD_GRAPH_STEPS captured steps where
+// launching them one by one is bound by the host: node sets of at most
+// RBFFD_GRAPH_TILES tiles, whose half steps take less than the 4 us of a launch,
+// and at least RBFFD_GRAPH_MIN_STEPS steps, which hide the capture (0.8 ms).
+// us per step of the 51^2 cavity, launched / replayed, runs one after another:
+// 100 steps 7.5 / 12.8, 200 steps 7.7 / 6.9, 1000 steps 8.0 / 6.6; on 40k nodes
+// (two 8 us kernels) 15.8 / 16.0 at 1000 steps.  rec(c, stream) records one full
+// step reading buffer set c; the buffers alternate within a graph and, its
+// steps being even, every replay leaves them as it found them.  *done receives
+// the number of steps replayed (even); the caller runs the rest.
 #define RBFFD_GRAPH_STEPS 64
-#define RBFFD_GRAPH_MIN_STEPS 512
+#define RBFFD_GRAPH_MIN_STEPS 192
+#define RBFFD_GRAPH_TILES 256
 template <typename Rec>
 int replay_steps(const rbffd_plan* p, int T, int cur, hipStream_t st, Rec rec, int* done) {
     *done = 0;
-    if (T < 4) return RBFFD_OK;
+    const int reps = T / RBFFD_GRAPH_STEPS;
+    if (reps < 1) return RBFFD_OK;
     hipStream_t cs;
     int rc = capture_stream(p, &cs);
     if (rc) return rc;
-    int left = T;
-    while (left >= 4) {
-        const int S = std::min(left & ~1, RBFFD_GRAPH_STEPS);
-        hipGraph_t g;
-        hipGraphExec_t ge;
-        HIPCHK(p, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < S; ++k) rec((cur + k) & 1, cs);
-        HIPCHK(p, hipStreamEndCapture(cs, &g));
-        HIPCHK(p, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
-        const int reps = left / S;
-        for (int r = 0; r < reps; ++r) HIPCHK(p, hipGraphLaunch(ge, st));
-        HIPCHK(p, hipGraphExecDestroy(ge));
-        HIPCHK(p, hipGraphDestroy(g));
-        left -= reps * S;
-        *done += reps * S;
-    }
+    hipGraph_t g;
+    hipGraphExec_t ge;
+    HIPCHK(p, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+    for (int k = 0; k < RBFFD_GRAPH_STEPS; ++k) rec((cur + k) & 1, cs);
+    HIPCHK(p, hipStreamEndCapture(cs, &g));
+    HIPCHK(p, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
+    for (int r = 0; r < reps; ++r) HIPCHK(p, hipGraphLaunch(ge, st));
+    HIPCHK(p, hipGraphExecDestroy(ge));
+    HIPCHK(p, hipGraphDestroy(g));
+    *done = reps * RBFFD_GRAPH_STEPS;
     return RBFFD_OK;
 }
 

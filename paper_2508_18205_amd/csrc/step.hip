@@ -2095,7 +2095,7 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
     if (a->ckpt && a->ckpt_every <= 0) return set_err(p, RBFFD_EINVAL, "ckpt_every must be positive");
     if (a->energy_out && a->energy_every < 0) return set_err(p, RBFFD_EINVAL, "energy_every < 0");
     RunWS w = run_ws(ws);
-    const bool graphs = a->use_graph && a->n_src <= 0 && a->n_rcv <= 0;
+    const bool graphs = a->use_graph && a->n_src <= 0 && a->n_rcv <= 0 && p->opE.tiles <= RBFFD_GRAPH_TILES;
     int c = f->cur;
     for (int n = 0; n < a->T;) {
         const int plain = graphs ? plain_steps(a, n) : 0;
