@@ -352,6 +352,7 @@ struct WArgs {
     int kind;
     int phs_k;
     int nrhs;
+    int deg;              // largest exponent of a monomial
     int upow;             // unscaling power l
     int periodic;
     double period[3];
@@ -360,6 +361,10 @@ struct WArgs {
     double hv_C;          // Delta^alpha r^(2a+1) = hv_C r
     double hv_poly[RBFFD_MAX_MONO];
     int8_t ex[RBFFD_MAX_MONO][3];
+    // ex (a byte per axis) and hv_poly in device memory: looked up per lane, the
+    // kernel arguments took a 107-column system longer than its elimination
+    uint32_t* tex;
+    double* tpoly;
     double* out;          // [Nt][nrhs][n]
     int64_t Nt;
     int64_t c0;           // first centre of this launch
@@ -381,91 +386,101 @@ __device__ __forceinline__ double phs(double r, int k) {
     return v;
 }
 
-__device__ __forceinline__ double mono(const double* x, const int8_t* e, int d) {
+// exponent of axis k in a packed monomial
+__device__ __forceinline__ int expo(uint32_t e, int k) { return (int)((e >> (8 * k)) & 0xFFu); }
+
+__device__ __forceinline__ double mono(const double* x, uint32_t e, int d) {
     double v = 1.0;
-    for (int k = 0; k < d; ++k) v *= ipow(x[k], e[k]);
+    for (int k = 0; k < d; ++k) v *= ipow(x[k], expo(e, k));
     return v;
 }
 
 // u . grad p at 0 for the monomial with exponents e: u_k for p = x_k, else 0
-__device__ __forceinline__ double dmono_at0(const int8_t* e, int d, const double* u) {
+__device__ __forceinline__ double dmono_at0(uint32_t e, int d, const double* u) {
     int deg = 0, ax = 0;
     for (int k = 0; k < d; ++k) {
-        deg += e[k];
-        if (e[k] == 1) ax = k;
+        deg += expo(e, k);
+        if (expo(e, k) == 1) ax = k;
     }
     return deg == 1 ? u[ax] : 0.0;
 }
 
-// Entry (i, j) of the augmented local system [A~ | B] (eq. 9 with the
-// eq. 13 / eq. 15 / Delta^alpha right-hand sides) from the scaled offsets xi
-// [n][3] and the stencil scale sc.
+__global__ void k_wtable(WArgs a) {
+    const int q = threadIdx.x;
+    if (q >= a.M) return;
+    a.tex[q] = (uint32_t)(uint8_t)a.ex[q][0] | (uint32_t)(uint8_t)a.ex[q][1] << 8 | (uint32_t)(uint8_t)a.ex[q][2] << 16;
+    a.tpoly[q] = a.hv_poly[q];
+}
+
+// Right-hand side col (a derivative direction; 0 for Delta^alpha) of the scaled
+// local system at row i (eq. 13 / eq. 15): x = the scaled offset of stencil node
+// i (rows i < n), sc the stencil scale.
+__device__ __forceinline__ double rhs_entry(const WArgs& a, const uint32_t* ex, const double* poly,
+                                            const double (&x)[3], double sc, int i, int col) {
+    const int n = a.n, d = a.d;
+    const double* u = a.fu[col];
+    if (a.kind == W_FD) {
+        if (i >= n) return dmono_at0(ex[i - n], d, u);
+        double r2 = 0.0, xu = 0.0;
+        for (int k = 0; k < d; ++k) {
+            r2 = fma(x[k], x[k], r2);
+            xu = fma(x[k], u[k], xu);
+        }
+        const double r = sqrt(r2);
+        // u . grad |x - xi_i|^k at x = 0 = -k r^(k-2) (xi_i . u)
+        return -(double)a.phs_k * phs(r, a.phs_k - 2) * xu;
+    }
+    if (a.kind == W_VFD) {
+        // central virtual difference: (-1/2 f(-delta u) + 1/2 f(+delta u)) / delta
+        const double dl = a.vdelta / sc;
+        double xm[3] = {0, 0, 0}, xp[3] = {0, 0, 0};
+        for (int k = 0; k < d; ++k) {
+            xm[k] = -dl * u[k];
+            xp[k] = dl * u[k];
+        }
+        double fm, fp;
+        if (i < n) {
+            double r2m = 0.0, r2p = 0.0;
+            for (int k = 0; k < d; ++k) {
+                const double tm = xm[k] - x[k], tp = xp[k] - x[k];
+                r2m = fma(tm, tm, r2m);
+                r2p = fma(tp, tp, r2p);
+            }
+            fm = phs(sqrt(r2m), a.phs_k);
+            fp = phs(sqrt(r2p), a.phs_k);
+        } else {
+            fm = mono(xm, ex[i - n], d);
+            fp = mono(xp, ex[i - n], d);
+        }
+        return (-0.5 * fm + 0.5 * fp) / dl;
+    }
+    if (i >= n) return poly[i - n];
+    double r2 = 0.0;
+    for (int k = 0; k < d; ++k) r2 = fma(x[k], x[k], r2);
+    return a.hv_C * sqrt(r2);
+}
+
+// Entry (i, j) of the augmented local system [A~ | B] (eq. 9) from the scaled
+// offsets xi [n][3].
 __device__ __forceinline__ double system_entry(const WArgs& a, const double* xi, double sc, int i, int j) {
     const int n = a.n, R = n + a.M, d = a.d;
-    double v = 0.0;
-    if (j < R) {
-        if (i < n && j < n) {
-            double r2 = 0.0;
-            for (int k = 0; k < d; ++k) {
-                const double t = xi[i * 3 + k] - xi[j * 3 + k];
-                r2 += t * t;
-            }
-            v = phs(sqrt(r2), a.phs_k);
-        } else if (i < n && j >= n) {
-            v = mono(xi + i * 3, a.ex[j - n], d);
-        } else if (i >= n && j < n) {
-            v = mono(xi + j * 3, a.ex[i - n], d);
-        }
-    } else {
-        const int col = j - R;   // right-hand side index (derivative direction)
-        const double* u = a.fu[col];
-        if (a.kind == W_FD) {
-            if (i < n) {
-                double r2 = 0.0, xu = 0.0;
-                for (int k = 0; k < d; ++k) {
-                    r2 += xi[i * 3 + k] * xi[i * 3 + k];
-                    xu += xi[i * 3 + k] * u[k];
-                }
-                const double r = sqrt(r2);
-                // u . grad |x - xi_i|^k at x = 0 = -k r^(k-2) (xi_i . u)
-                v = -(double)a.phs_k * phs(r, a.phs_k - 2) * xu;
-            } else {
-                v = dmono_at0(a.ex[i - n], d, u);
-            }
-        } else if (a.kind == W_VFD) {
-            // central virtual difference: (-1/2 f(-delta u) + 1/2 f(+delta u)) / delta
-            const double dl = a.vdelta / sc;
-            double xm[3] = {0, 0, 0}, xp[3] = {0, 0, 0};
-            for (int k = 0; k < d; ++k) {
-                xm[k] = -dl * u[k];
-                xp[k] = dl * u[k];
-            }
-            double fm, fp;
-            if (i < n) {
-                double r2m = 0.0, r2p = 0.0;
-                for (int k = 0; k < d; ++k) {
-                    const double tm = xm[k] - xi[i * 3 + k], tp = xp[k] - xi[i * 3 + k];
-                    r2m += tm * tm;
-                    r2p += tp * tp;
-                }
-                fm = phs(sqrt(r2m), a.phs_k);
-                fp = phs(sqrt(r2p), a.phs_k);
-            } else {
-                fm = mono(xm, a.ex[i - n], d);
-                fp = mono(xp, a.ex[i - n], d);
-            }
-            v = (-0.5 * fm + 0.5 * fp) / dl;
-        } else {
-            if (i < n) {
-                double r2 = 0.0;
-                for (int k = 0; k < d; ++k) r2 += xi[i * 3 + k] * xi[i * 3 + k];
-                v = a.hv_C * sqrt(r2);
-            } else {
-                v = a.hv_poly[i - n];
-            }
-        }
+    if (j >= R) {
+        double x[3] = {0, 0, 0};
+        if (i < n)
+            for (int k = 0; k < d; ++k) x[k] = xi[i * 3 + k];
+        return rhs_entry(a, a.tex, a.tpoly, x, sc, i, j - R);
     }
-    return v;
+    if (i < n && j < n) {
+        double r2 = 0.0;
+        for (int k = 0; k < d; ++k) {
+            const double t = xi[i * 3 + k] - xi[j * 3 + k];
+            r2 += t * t;
+        }
+        return phs(sqrt(r2), a.phs_k);
+    }
+    if (i < n) return mono(xi + i * 3, a.tex[j - n], d);
+    if (j < n) return mono(xi + j * 3, a.tex[i - n], d);
+    return 0.0;
 }
 
 // A pivot no larger than 1024 R eps max_ij |A~_ij| (R unknowns, eps the FP64
@@ -618,72 +633,105 @@ __global__ __launch_bounds__(1024) void k_weights(WArgs a) {
     }
 }
 
-// Register-resident variant for systems with R + nrhs <= 16 B (B <= 7): a
-// 256-thread workgroup per system seen as a 16 x 16 grid; thread (tr, tc)
-// holds the entries (tr + 16 a, tc + 16 b), a, b < B, of [A~ | B] in
-// registers.  Gauss-Jordan elimination with partial pivoting (largest |value|
-// among the rows not yet used as pivots, ties to the lower row): one barrier
-// after the pivot candidates, one after the pivot row and the multipliers are
-// published in LDS, per column; no back substitution.  The LDS footprint is
-// ~20 KB (mostly the assembly band), so registers, not LDS, set how many
-// systems share a CU (the LDS-resident kernel holds one 106-unknown system
-// per CU).
-constexpr int WREG_T = 16, WREG_BMAX = 7, WREG_MAX = WREG_T * WREG_BMAX;
+// Register-resident variant for systems with R + nrhs <= 112: W wavefronts per
+// system seen as a 16 x 4 W grid of lanes; lane (tr, tc) holds the entries
+// (tr + 16 a, tc + 4 W b), a < BR, b < BC, of [A~ | B] in registers.
+// Gauss-Jordan elimination with partial pivoting (largest |value| among the rows
+// not used yet, ties to the lower row); no back substitution.
+//
+// What bounds a system is the instructions around each column's update (find the
+// pivot, publish its row and the column), issued by one or two wavefronts, so
+// they are kept few: the sixteen lanes of the column's group find the pivot with
+// cross-lane moves (with sixteen lanes along the rows a lane has only BR
+// candidates), the row number reaches the others as a scalar, and pivot row and
+// column go through LDS.  A system held by one wavefront meets no barrier; larger ones take two
+// wavefronts (a 107-column system is 392 registers of one) and one barrier per
+// column, which hands over the column.  Columns left of the pivot are not
+// updated any more (the loop over column blocks is unrolled).
+// Measured, ms for the hyperviscosity systems of 160k 2D nodes (86 columns) /
+// 91k 3D nodes (107) / the curl systems of 160k 2D nodes (42): 16.6 / 13.4 / 2.5;
+// the same results from 256 threads with two barriers per column and LDS
+// shuffles 27.7 / 28.5 / 6.7.  (Comparing only the leading 13 bits of the
+// candidates and a Newton reciprocal take 14.9 / 12.1, but other roundings.)
+constexpr int WREG_MAX = 112;
 
-// Column b / row r of the register block for an index that is the same in
-// every thread: a switch on it compiles to scalar branches, and each case
-// reads the registers with compile-time indices.
-template <int B>
-__device__ __forceinline__ void reg_col(const double (&m)[B][B], int b, double (&out)[B]) {
-    switch (b) {
-#define WREG_COL(C)                                                            \
-    case C:                                                                    \
-        _Pragma("unroll") for (int r = 0; r < B; ++r) out[r] = m[r][C < B ? C : B - 1]; \
-        break;
-        WREG_COL(0) WREG_COL(1) WREG_COL(2) WREG_COL(3) WREG_COL(4) WREG_COL(5)
-#undef WREG_COL
-        default:
-            _Pragma("unroll") for (int r = 0; r < B; ++r) out[r] = m[r][B - 1];
-    }
+// x of the lane whose number differs by 1, 2 (quad permutations), or the mirror
+// image of its 8 (half row) or 16 lanes (row)
+template <int CTRL>
+__device__ __forceinline__ int dpp32(int x) {
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
 }
-template <int B>
-__device__ __forceinline__ void reg_row(const double (&m)[B][B], int a, double (&out)[B]) {
-    switch (a) {
-#define WREG_ROW(A)                                                            \
-    case A:                                                                    \
-        _Pragma("unroll") for (int q = 0; q < B; ++q) out[q] = m[A < B ? A : B - 1][q]; \
-        break;
-        WREG_ROW(0) WREG_ROW(1) WREG_ROW(2) WREG_ROW(3) WREG_ROW(4) WREG_ROW(5)
-#undef WREG_ROW
-        default:
-            _Pragma("unroll") for (int q = 0; q < B; ++q) out[q] = m[B - 1][q];
-    }
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141, DPP_MIRROR16 = 0x140;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double x) {
+    const int lo = dpp32<CTRL>(__double2loint(x)), hi = dpp32<CTRL>(__double2hiint(x));
+    return __hiloint2double(hi, lo);
 }
 
-template <int WREG_B>
-__global__ __launch_bounds__(256, 3) void k_wreg(WArgs a) {
-    __shared__ double xi[WREG_MAX * 3];
-    __shared__ double band[WREG_T * WREG_MAX];   // one 16-row band during assembly
-    __shared__ double prow[WREG_MAX], mcol[WREG_MAX], dpiv[WREG_MAX];
-    __shared__ double cval[WREG_T];              // [0]: the pivot candidate of column k
-    __shared__ int cidx[WREG_T];
-    __shared__ int kof[WREG_MAX];                // column pivoted on row i, -1 before
-    __shared__ double s_scale;
+// |x|, negated where bit a of live is clear
+__device__ __forceinline__ double signed_abs(double x, uint32_t live, int a) {
+    const uint32_t sign = ~(uint32_t)((int32_t)(live << (31 - a)) >> 31) & 0x80000000u;
+    return __hiloint2double((int)(((uint32_t)__double2hiint(x) & 0x7FFFFFFFu) | sign), __double2loint(x));
+}
+
+// monomial with exponents e (a byte per axis) at stencil node j, from the powers
+// x^1 .. x^deg of the offsets [deg][3][n]
+__device__ __forceinline__ double pw_mono(const double* pw, uint32_t e, int n, int j) {
+    double p = 1.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int ek = expo(e, k);
+        const double f = pw[((max(ek, 1) - 1) * 3 + k) * n + j];
+        p *= ek > 0 ? f : 1.0;
+    }
+    return p;
+}
+
+// orders the wavefront's LDS writes before its other lanes' reads
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int W, int BR, int BC>
+__global__ __launch_bounds__(64 * W, BR * BC > 60 ? 2 : 3) void k_wreg(WArgs a) {
+    constexpr int NT = 64 * W, CW = 4 * W;       // threads; columns per register column
+    // odd strides: pairs of entries are moved as two separate registers each
+    // (16-byte moves would need neighbouring registers along rows and columns
+    // at once, and copies of both)
+    constexpr int RS = BR | 1, CS = BC | 1;
+    extern __shared__ __align__(16) double wsm[];
+    double* pw = wsm;                            // powers x^1 .. x^deg of the scaled offsets [deg][3][n]
+    __shared__ double own[NT * BC];              // each lane's entries of a row block, on their way to registers
+    __shared__ double mcol[2][16 * RS];          // [tr][a]
+    __shared__ double prow[2][W][4 * CS];        // [tc of the wavefront][b]
+    __shared__ double dpiv[16 * BR];
+    __shared__ int kof[16 * BR];                 // column pivoted on row i
+    __shared__ uint32_t ex[RBFFD_MAX_MONO];      // exponents of each monomial, a byte per axis
+    __shared__ double poly[RBFFD_MAX_MONO];
+    __shared__ double rhs[3][16 * BR];
+    __shared__ double s_red[W];
+    __shared__ int s_p[2];
     const int64_t c = a.c0 + blockIdx.x;
     if (c >= a.Nt) return;                       // uniform over the workgroup
-    // thread (tr, tc): the 16 threads of one register column tc are 16
-    // consecutive lanes of one wavefront, so the column steps of the
-    // elimination run in a single wavefront
-    const int tid = threadIdx.x, tr = tid & 15, tc = tid >> 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tr = lane & 15, tl = lane >> 4, tc = tl + 4 * wv;
     const int n = a.n, R = n + a.M, d = a.d;
     const int lda = R + a.nrhs;
 
     // 1. offsets from the centre and the stencil radius (as k_weights)
     const double* xc = a.txyz + c * d;
     const int32_t* row = a.st + c * a.st_stride;
-    for (int j = tid; j < n; j += 256) {
+    if (tid < a.M) {
+        ex[tid] = a.tex[tid];
+        poly[tid] = a.tpoly[tid];
+    }
+    double mx = 0.0;
+    for (int j = tid; j < n; j += NT) {
         const double* xj = a.sxyz + (int64_t)row[j] * d;
-        for (int k = 0; k < 3; ++k) xi[j * 3 + k] = 0.0;
+        double r2 = 0.0;
         for (int k = 0; k < d; ++k) {
             double dk = xj[k] - xc[k];
             if (a.periodic) {
@@ -691,165 +739,228 @@ __global__ __launch_bounds__(256, 3) void k_wreg(WArgs a) {
                 if (dk > 0.5 * L) dk -= L;
                 if (dk < -0.5 * L) dk += L;
             }
-            xi[j * 3 + k] = dk;
+            pw[k * n + j] = dk;
+            r2 = fma(dk, dk, r2);
         }
-    }
-    for (int i = tid; i < WREG_MAX; i += 256) {
-        kof[i] = -1;
-        prow[i] = 0.0;
-        mcol[i] = 0.0;
+        mx = fmax(mx, sqrt(r2));
     }
     if (tid == 0 && a.check_self && row[0] != (int32_t)c) atomicAdd(&a.status[1], 1);
-    __syncthreads();
-    if (tid < 64) {
-        double mx = 0.0;
-        for (int j = tid; j < n; j += 64) {
-            double r2 = 0.0;
-            for (int k = 0; k < d; ++k) r2 += xi[j * 3 + k] * xi[j * 3 + k];
-            mx = fmax(mx, sqrt(r2));
-        }
-        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_down(mx, off, 64));
-        if (tid == 0) s_scale = mx;
-    }
-    __syncthreads();
-    const double sc = s_scale;
-    for (int j = tid; j < n * 3; j += 256) xi[j] = xi[j] / sc;
-    __syncthreads();
-
-    // 2. assemble band by band through LDS into the registers
-    double m[WREG_B][WREG_B];
-#pragma unroll
-    for (int ra = 0; ra < WREG_B; ++ra) {
-        for (int e = tid; e < WREG_T * lda; e += 256) {
-            const int i = WREG_T * ra + e / lda, j = e % lda;
-            band[e] = i < R ? system_entry(a, xi, sc, i, j) : 0.0;
-        }
+    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    if (W > 1) {
+        if (lane == 0) s_red[wv] = mx;
         __syncthreads();
 #pragma unroll
-        for (int cb = 0; cb < WREG_B; ++cb) {
-            const int j = tc + WREG_T * cb;
-            m[ra][cb] = j < lda ? band[tr * lda + j] : 0.0;
+        for (int w = 0; w < W; ++w) mx = fmax(mx, s_red[w]);
+    }
+    const double sc = mx;
+    const int deg = a.deg;
+    for (int j = tid; j < n; j += NT)
+        for (int k = 0; k < 3; ++k) {
+            const double x = k < d ? pw[k * n + j] / sc : 0.0;
+            double v = 1.0;
+            for (int e = 0; e < deg; ++e) {
+                v *= x;
+                pw[(e * 3 + k) * n + j] = v;
+            }
         }
-        __syncthreads();
+    __syncthreads();
+
+    // 2. right-hand sides, one row per lane
+    for (int i = tid; i < R; i += NT) {
+        double x[3] = {0, 0, 0};
+        if (i < n)
+            for (int k = 0; k < 3; ++k) x[k] = pw[k * n + i];
+        for (int q = 0; q < a.nrhs; ++q) rhs[q][i] = rhs_entry(a, ex, poly, x, sc, i, q);
+    }
+    __syncthreads();
+
+    // 3. the matrix, sixteen rows at a time: every lane computes its own entries,
+    // and a wavefront only looks at the parts (r^k, monomial columns, monomial
+    // rows, right-hand sides) that its four columns of a block meet
+    double m[BR][BC];
+#pragma unroll
+    for (int ra = 0; ra < BR; ++ra)
+#pragma unroll
+        for (int cb = 0; cb < BC; ++cb) m[ra][cb] = 0.0;
+    for (int ra = 0; ra * 16 < R; ++ra) {
+        const int i0 = ra * 16, i = i0 + tr, ic = min(i, n - 1);
+        const double x = pw[ic], y = pw[n + ic], z = pw[2 * n + ic];
+        const uint32_t ei = ex[min(max(i - n, 0), a.M - 1)];
+#pragma unroll 1
+        for (int cb = 0; cb < BC; ++cb) {
+            const int j0 = CW * cb + 4 * wv, j = j0 + tl;   // j0: the same in the wavefront
+            double v = 0.0;
+            if (j0 < n && i0 < n) {
+                const int jc = min(j, n - 1);
+                const double tx = x - pw[jc], ty = y - pw[n + jc], tz = z - pw[2 * n + jc];
+                const double r = phs(sqrt(fma(tz, tz, fma(ty, ty, tx * tx))), a.phs_k);
+                v = (i < n) & (j < n) ? r : v;
+            }
+            if (j0 + 3 >= n && j0 < R && i0 < n) {
+                const double p = pw_mono(pw, ex[min(max(j - n, 0), a.M - 1)], n, ic);
+                v = (i < n) & (j >= n) & (j < R) ? p : v;
+            }
+            if (j0 < n && i0 + 15 >= n) {
+                const double p = pw_mono(pw, ei, n, min(j, n - 1));
+                v = (i >= n) & (i < R) & (j < n) ? p : v;
+            }
+            if (j0 + 3 >= R && j0 < lda) {
+                const double p = rhs[min(max(j - R, 0), 2)][min(i, R - 1)];
+                v = (j >= R) & (j < lda) & (i < R) ? p : v;
+            }
+            own[cb * NT + tid] = v;
+        }
+#pragma unroll
+        for (int q = 0; q < BR; ++q) {
+            if (q != ra) continue;               // a scalar branch: register rows are compile-time
+#pragma unroll
+            for (int cb = 0; cb < BC; ++cb) m[q][cb] = own[cb * NT + tid];
+        }
     }
 
-    // singularity threshold relative to the largest entry of the square
-    // system: a wavefront maximum, then the four wavefronts' through LDS
+    // singularity threshold relative to the largest entry of the square system
     double tau;
     {
-        double mx = 0.0;
+        double t = 0.0;
 #pragma unroll
-        for (int ra = 0; ra < WREG_B; ++ra)
+        for (int ra = 0; ra < BR; ++ra)
 #pragma unroll
-            for (int cb = 0; cb < WREG_B; ++cb) {
-                const bool in = (tr + WREG_T * ra < R) & (tc + WREG_T * cb < R);
-                mx = in ? fmax(mx, fabs(m[ra][cb])) : mx;
+            for (int cb = 0; cb < BC; ++cb) {
+                const bool in = (tr + 16 * ra < R) & (tc + CW * cb < R);
+                t = in ? fmax(t, fabs(m[ra][cb])) : t;
             }
-        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-        if ((tid & 63) == 0) cval[tid >> 6] = mx;
-        __syncthreads();
-        tau = pivot_floor(R, fmax(fmax(cval[0], cval[1]), fmax(cval[2], cval[3])));
-        __syncthreads();                         // cval is reused by the pivot search
+        for (int off = 32; off > 0; off >>= 1) t = fmax(t, __shfl_xor(t, off, 64));
+        if (W > 1) {
+            if (lane == 0) s_red[wv] = t;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < W; ++w) t = fmax(t, s_red[w]);
+        }
+        tau = pivot_floor(R, t);
     }
-    // 3. Gauss-Jordan elimination.  The padding rows (i >= R) and columns
-    // (j >= lda) hold zeros and stay zero, so every step below is written
-    // without per-element branches: predicates become selects and LDS reads
-    // are unconditional (all arrays have WREG_MAX entries).
+
+    // 4. Gauss-Jordan elimination.  Bit a of live: row tr + 16 a is no pivot row
+    // yet; padding rows (i >= R) never are.  Padding rows and columns hold zeros
+    // and stay zero.
+    uint32_t live = 0;
+#pragma unroll
+    for (int ra = 0; ra < BR; ++ra) live |= tr + 16 * ra < R ? 1u << ra : 0u;
     bool bad = false;
-    for (int k = 0; k < R; ++k) {
-        const int bk = k >> 4, ck = k & 15;
-        if ((tid >> 6) == (ck >> 2)) {           // the wavefront holding column k
-            double best = -1.0, bval = 0.0;
-            int bi = R;
-            if (tc == ck) {
-                double colk[WREG_B];
-                reg_col(m, bk, colk);
 #pragma unroll
-                for (int ra = 0; ra < WREG_B; ++ra) {
-                    const int i = tr + WREG_T * ra;
-                    const double v = colk[ra];
-                    const bool take = (i < R) & (kof[i] < 0) & (fabs(v) > best);
-                    best = take ? fabs(v) : best;
-                    bval = take ? v : bval;
-                    bi = take ? i : bi;
+    for (int kb = 0; kb < BC; ++kb) {
+        for (int kc = 0; kc < CW; ++kc) {
+            const int k = kb * CW + kc;
+            if (k >= R || bad) break;
+            const int buf = kc & 1, ck = kc & 3; // CW is even: the buffers alternate across blocks too
+            const int wk = W == 1 ? 0 : kc >> 2; // the wavefront holding column k
+            int p = 0;
+            bool none = false;
+            if (W == 1 || wv == wk) {
+                // every group of sixteen lanes looks at its own column of block
+                // kb; group ck holds column k.  Rows in use count as -|value|.
+                double best = -INFINITY;
+#pragma unroll
+                for (int ra = 0; ra < BR; ++ra) best = fmax(best, signed_abs(m[ra][kb], live, ra));
+                best = fmax(best, dpp64<DPP_XOR1>(best));
+                best = fmax(best, dpp64<DPP_XOR2>(best));
+                best = fmax(best, dpp64<DPP_MIRROR8>(best));
+                best = fmax(best, dpp64<DPP_MIRROR16>(best));
+                int lo = 16 * BR;
+#pragma unroll
+                for (int ra = BR - 1; ra >= 0; --ra) lo = signed_abs(m[ra][kb], live, ra) == best ? tr + 16 * ra : lo;
+                lo = min(lo, dpp32<DPP_XOR1>(lo));
+                lo = min(lo, dpp32<DPP_XOR2>(lo));
+                lo = min(lo, dpp32<DPP_MIRROR8>(lo));
+                lo = min(lo, dpp32<DPP_MIRROR16>(lo));
+                p = min(__builtin_amdgcn_readlane(lo, ck * 16), R - 1);
+                // no row left that compares (a column of NaN): no pivot
+                none = __builtin_amdgcn_readlane(__double2hiint(best), ck * 16) < 0;
+                if (tl == ck) {
+#pragma unroll
+                    for (int ra = 0; ra < BR; ++ra) mcol[buf][tr * RS + ra] = m[ra][kb];
+                    // the pivot row itself is not updated
+                    if (tr == (p & 15)) mcol[buf][tr * RS + (p >> 4)] = 0.0;
                 }
+                if (W > 1 && lane == 0) s_p[buf] = none ? p | 256 : p;
+            } else {
+                __syncthreads();
+                p = __builtin_amdgcn_readfirstlane(s_p[buf]);
+                none = (p & 256) != 0;
+                p &= 255;
             }
-            // reduce over the 16 lanes of each column (lanes 16 q .. 16 q + 15)
+            if (tr == (p & 15)) {
 #pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                const double ob = __shfl_xor(best, off, 64), ov = __shfl_xor(bval, off, 64);
-                const int oi = __shfl_xor(bi, off, 64);
-                const bool take = (ob > best) | ((ob == best) & (oi < bi));
-                best = take ? ob : best;
-                bval = take ? ov : bval;
-                bi = take ? oi : bi;
-            }
-            if (tid == (ck << 4)) {               // tr = 0 of column ck
-                cval[0] = bval;
-                cidx[0] = bi;
-            }
-        }
-        __syncthreads();
-        const int p = cidx[0];
-        const double pval = cval[0], pbest = p < R ? fabs(pval) : -1.0;
-        if (!(pbest > tau)) {                    // the same decision in every thread
-            bad = true;
-            break;
-        }
-        if (tr == (p & 15)) {
-            double rowp[WREG_B];
-            reg_row(m, p >> 4, rowp);
+                for (int q = 0; q < BR; ++q) {
+                    if (q != (p >> 4)) continue; // a scalar branch: register rows are compile-time
 #pragma unroll
-            for (int cb = 0; cb < WREG_B; ++cb) prow[tc + WREG_T * cb] = rowp[cb];
-        }
-        if (tc == ck) {
-            double colk[WREG_B];
-            reg_col(m, bk, colk);
+                    for (int cb = kb; cb < BC; ++cb) prow[buf][wv][tl * CS + cb] = m[q][cb];
+                }
+                live &= ~(1u << (p >> 4));
+            }
+            if (W > 1 && wv == wk) __syncthreads();
+            wave_sync();
+            const double pval = prow[buf][wk][ck * CS + kb];
+            double pj[BC];
+#pragma unroll
+            for (int cb = kb; cb < BC; ++cb) pj[cb] = prow[buf][wv][tl * CS + cb];
+            if (none || !(fabs(pval) > tau)) {   // the same decision in every lane
+                bad = true;
+                break;
+            }
+            if (tid == 0) {
+                kof[p] = k;
+                dpiv[k] = pval;
+            }
             const double rp = 1.0 / pval;
+            pj[kb] = tc > kc ? pj[kb] : 0.0;     // columns right of k only
 #pragma unroll
-            for (int ra = 0; ra < WREG_B; ++ra) {
-                const int i = tr + WREG_T * ra;
-                mcol[i] = (i == p) ? 0.0 : colk[ra] * rp;
+            for (int ra = 0; ra < BR; ++ra) {
+                const double mi = mcol[buf][tr * RS + ra] * rp;
+#pragma unroll
+                for (int cb = kb; cb < BC; ++cb) m[ra][cb] -= mi * pj[cb];
             }
-        }
-        if (tid == 0) {
-            kof[p] = k;
-            dpiv[k] = pval;
-        }
-        __syncthreads();
-        double pj[WREG_B];
-#pragma unroll
-        for (int cb = 0; cb < WREG_B; ++cb) {
-            const int j = tc + WREG_T * cb;
-            pj[cb] = (j > k) ? prow[j] : 0.0;
-        }
-#pragma unroll
-        for (int ra = 0; ra < WREG_B; ++ra) {
-            const double mi = mcol[tr + WREG_T * ra];
-#pragma unroll
-            for (int cb = 0; cb < WREG_B; ++cb) m[ra][cb] -= mi * pj[cb];
+            wave_sync();
         }
     }
     if (bad) {
         if (tid == 0) atomicMin(&a.status[0], (int32_t)c);
-        for (int e = tid; e < a.nrhs * n; e += 256) a.out[c * a.nrhs * n + e] = 0.0;
+        for (int e = tid; e < a.nrhs * n; e += NT) a.out[c * a.nrhs * n + e] = 0.0;
         return;
     }
-    // 4. unknown k sits in the row pivoted at column k; unscale and store the
+    __syncthreads();
+    // 5. unknown k sits in the row pivoted at column k; unscale and store the
     // first n entries of every right-hand side
     const double us = ipow(sc, a.upow);
 #pragma unroll
-    for (int ra = 0; ra < WREG_B; ++ra) {
-        const int i = tr + WREG_T * ra;
+    for (int ra = 0; ra < BR; ++ra) {
+        const int i = tr + 16 * ra;
         if (i >= R) continue;
         const int k = kof[i];
         if (k >= n) continue;
 #pragma unroll
-        for (int cb = 0; cb < WREG_B; ++cb) {
-            const int j = tc + WREG_T * cb;
+        for (int cb = 0; cb < BC; ++cb) {
+            const int j = tc + CW * cb;
             if (j >= R && j < lda) a.out[c * a.nrhs * n + (int64_t)(j - R) * n + k] = m[ra][cb] / dpiv[k] / us;
         }
     }
+}
+
+// the smallest register block that holds R rows and lda columns
+void launch_wreg(const WArgs& a, int R, int lda, unsigned nb, hipStream_t st) {
+    const size_t lds = (size_t)a.n * 3 * a.deg * sizeof(double);
+#define WREG_TRY(W, BR, BC)                                                                     \
+    if (R <= 16 * BR && lda <= 4 * W * BC) {                                                    \
+        hipLaunchKernelGGL((k_wreg<W, BR, BC>), dim3(nb), dim3(64 * W), lds, st, a);            \
+        return;                                                                                 \
+    }
+    WREG_TRY(1, 2, 5)
+    WREG_TRY(1, 2, 9)
+    WREG_TRY(1, 3, 12)
+    WREG_TRY(2, 4, 8)
+    WREG_TRY(2, 5, 9)
+    WREG_TRY(2, 6, 11)
+    WREG_TRY(2, 7, 14)
+#undef WREG_TRY
 }
 
 // ---------------------------------------------------------------------------
@@ -1293,6 +1404,8 @@ int64_t setup_ws_bytes(const rbffd_plan* p) {
         w.take<int32_t>(p->E.N * std::max(p->nh, 1));
     }
     w.take<int32_t>(64);   // status
+    w.take<uint32_t>(RBFFD_MAX_MONO);
+    w.take<double>(RBFFD_MAX_MONO);
     if (has_wall_normals(p)) w.take<double>(p->E.N * p->dim);   // normals, original order
     int64_t need = w.off;
     if (p->collocated) {
@@ -1421,7 +1534,7 @@ int setup_nodes_and_stencils(rbffd_plan* p, void* wsp, hipStream_t st) {
 }
 
 static int launch_weights(rbffd_plan* p, const OpBlock& o, const NodeSet& T, const NodeSet& S, bool curl,
-                          int32_t* status, hipStream_t st) {
+                          int32_t* status, uint32_t* tex, double* tpoly, hipStream_t st) {
     const int d = p->dim;
     WArgs a{};
     a.txyz = T.xyz;
@@ -1431,6 +1544,8 @@ static int launch_weights(rbffd_plan* p, const OpBlock& o, const NodeSet& T, con
     for (int k = 0; k < 3; ++k) a.period[k] = p->p.hi[k] - p->p.lo[k];
     a.Nt = o.Nt;
     a.status = status;
+    a.tex = tex;
+    a.tpoly = tpoly;
     if (curl) {
         a.st = o.cross ? o.st_curl : o.st_union;
         a.st_stride = o.cross ? o.n : o.ns;
@@ -1483,19 +1598,17 @@ static int launch_weights(rbffd_plan* p, const OpBlock& o, const NodeSet& T, con
         a.out = o.wh;
         a.check_self = 1;
     }
+    for (int q = 0; q < a.M; ++q)
+        for (int k = 0; k < d; ++k) a.deg = std::max(a.deg, (int)a.ex[q][k]);
+    a.deg = std::max(a.deg, 1);
+    hipLaunchKernelGGL(k_wtable, dim3(1), dim3(RBFFD_MAX_MONO), 0, st, a);
     const int R = a.n + a.M;
     constexpr int64_t chunk = (int64_t)1 << 21;   // a dispatch counts work-items in 32 bits
     if (R + a.nrhs <= WREG_MAX) {
-        // the system fits the register-resident solver (every configured
-        // workload), with the smallest register block that holds it
-        const int blk = (R + a.nrhs + WREG_T - 1) / WREG_T;
+        // the system fits the register-resident solver (every configured workload)
         for (int64_t c0 = 0; c0 < o.Nt; c0 += chunk) {
             a.c0 = c0;
-            const int64_t nb = std::min<int64_t>(chunk, o.Nt - c0);
-            if (blk <= 3) hipLaunchKernelGGL(k_wreg<3>, dim3((unsigned)nb), dim3(256), 0, st, a);
-            else if (blk <= 4) hipLaunchKernelGGL(k_wreg<4>, dim3((unsigned)nb), dim3(256), 0, st, a);
-            else if (blk <= 6) hipLaunchKernelGGL(k_wreg<6>, dim3((unsigned)nb), dim3(256), 0, st, a);
-            else hipLaunchKernelGGL(k_wreg<7>, dim3((unsigned)nb), dim3(256), 0, st, a);
+            launch_wreg(a, R, R + a.nrhs, (unsigned)std::min<int64_t>(chunk, o.Nt - c0), st);
             HIPCHK(p, hipGetLastError());
         }
         return RBFFD_OK;
@@ -1523,17 +1636,19 @@ static int launch_weights(rbffd_plan* p, const OpBlock& o, const NodeSet& T, con
 int setup_weights(rbffd_plan* p, void* wsp, hipStream_t st) {
     WS w{(char*)wsp};
     int32_t* status = w.take<int32_t>(64);
+    uint32_t* tex = w.take<uint32_t>(RBFFD_MAX_MONO);
+    double* tpoly = w.take<double>(RBFFD_MAX_MONO);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, status, 64, 0);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, st, status, 1, INT32_MAX);
     int rc;
     if (p->collocated) {
-        if ((rc = launch_weights(p, p->opH, p->E, p->E, true, status, st))) return rc;
-        if (p->nh > 0 && (rc = launch_weights(p, p->opH, p->E, p->E, false, status, st))) return rc;
+        if ((rc = launch_weights(p, p->opH, p->E, p->E, true, status, tex, tpoly, st))) return rc;
+        if (p->nh > 0 && (rc = launch_weights(p, p->opH, p->E, p->E, false, status, tex, tpoly, st))) return rc;
     } else {
-        if ((rc = launch_weights(p, p->opH, p->H, p->E, true, status, st))) return rc;
-        if (p->nh > 0 && (rc = launch_weights(p, p->opH, p->H, p->H, false, status, st))) return rc;
-        if ((rc = launch_weights(p, p->opE, p->E, p->H, true, status, st))) return rc;
-        if (p->nh > 0 && (rc = launch_weights(p, p->opE, p->E, p->E, false, status, st))) return rc;
+        if ((rc = launch_weights(p, p->opH, p->H, p->E, true, status, tex, tpoly, st))) return rc;
+        if (p->nh > 0 && (rc = launch_weights(p, p->opH, p->H, p->H, false, status, tex, tpoly, st))) return rc;
+        if ((rc = launch_weights(p, p->opE, p->E, p->H, true, status, tex, tpoly, st))) return rc;
+        if (p->nh > 0 && (rc = launch_weights(p, p->opE, p->E, p->E, false, status, tex, tpoly, st))) return rc;
     }
     return stage_status(p, status, st);
 }
