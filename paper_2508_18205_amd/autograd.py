@@ -28,8 +28,7 @@ class MaxwellFn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, eps_r, amp, prob):
         s = prob.solver
-        N = s.N
-        st = s.state(np.zeros((N, s.fe)), np.zeros((N, s.fh)), eps_r=eps_r.detach().double().cpu().numpy())
+        st = s.state_at_rest(eps_r)
         amp_np = amp.detach().double().cpu().numpy()
         out = s.run(st, prob.T, src=(prob.src_nodes, amp_np, prob.src_wave), rcv=prob.rcv_nodes,
                     ckpt_every=prob.ckpt_every)
@@ -45,8 +44,8 @@ class MaxwellFn(torch.autograd.Function):
     def backward(ctx, grad_traces):
         prob = ctx.prob
         s = prob.solver
-        g_eps, g_amp = s.adjoint(ctx.st, prob.T, ctx.ckpt, prob.ckpt_every, grad_traces.detach(),
-                                 src=(prob.src_nodes, ctx.amp, prob.src_wave), rcv=prob.rcv_nodes)
-        ge = torch.as_tensor(g_eps).to(dtype=ctx.eps_meta[0], device=ctx.eps_meta[1])
-        ga = torch.as_tensor(g_amp).to(dtype=ctx.amp_meta[0], device=ctx.amp_meta[1])
+        g_eps, g_amp = s.adjoint_device(ctx.st, prob.T, ctx.ckpt, prob.ckpt_every, grad_traces.detach(),
+                                        src=(prob.src_nodes, ctx.amp, prob.src_wave), rcv=prob.rcv_nodes)
+        ge = g_eps.to(dtype=ctx.eps_meta[0], device=ctx.eps_meta[1])
+        ga = g_amp.to(dtype=ctx.amp_meta[0], device=ctx.amp_meta[1])
         return ge, ga, None

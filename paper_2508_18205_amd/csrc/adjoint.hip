@@ -47,6 +47,14 @@ struct AA {
     const T* En1;         // E^{n+1}
     const T* En;          // E^n
     double* geps;
+    // sources of the step whose node terms are taken, receivers of E^n
+    int n_src, n_rcv;
+    const int32_t* snode;
+    const T* samp;
+    const T* swave;       // [n_src] waveform row of that step
+    double* gamp;
+    const int32_t* rnode;
+    const T* gtr;         // [n_rcv] dJ/d(trace row of E^n)
 };
 
 template <typename T>
@@ -55,35 +63,76 @@ __device__ __forceinline__ double eps_of(const AA<T>& a, int64_t i) {
     return sizeof(T) == 8 ? ((const double*)a.eps_r)[i] : (double)((const float*)a.eps_r)[i];
 }
 
-// mu = P lambda_E, K mu, and the eps_r gradient (source term corrected later)
+// mu = P lambda_E, K mu, and what a reverse step adds to the gradients, at node i:
+//   dJ/deps_r -= (mu / eps_r) (E^{n+1} - E^n - s^{n+1}),  dJ/da_s += g_s^n mu
+// (one thread per node, sources in order, so no two threads meet).
 template <typename T>
-__global__ void k_adj1(AA<T> a) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.N) return;
+__device__ __forceinline__ void node_terms(const AA<T>& a, int64_t i, T lam) {
     const bool free_ = a.emask[i] & 1;
-    const T mu = free_ ? a.lamE[i] : (T)0;
+    const T mu = free_ ? lam : (T)0;
     const double er = eps_of(a, i);
     const T kap = (T)(a.dt / (a.eps0 * er));
     a.mu[i] = mu;
     a.kmu[i] = kap * mu;
-    if (free_) a.geps[i] += -((double)mu / er) * ((double)a.En1[i] - (double)a.En[i]);
+    double ge = a.geps[i];
+    if (free_) ge += -((double)mu / er) * ((double)a.En1[i] - (double)a.En[i]);
+    for (int s = 0; s < a.n_src; ++s) {
+        if (a.snode[s] != (int32_t)i) continue;
+        const double g = (double)a.swave[s];
+        a.gamp[s] += g * (double)mu;
+        if (free_) ge += ((double)mu / er) * ((double)a.samp[s] * g);
+    }
+    a.geps[i] = ge;
 }
+
+// the node terms of a step on their own: the first reverse step of a segment
+// (its E fields are recomputed only after the step before it in the sweep), and
+// every step where sources or receivers are too many to look through per node
+template <typename T>
+__global__ __launch_bounds__(256) void k_adj1(AA<T> a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < a.N) node_terms(a, i, a.lamE[i]);
+}
+
+// Gathers with the transposed operators.  A node's entries are a chain of index,
+// value, sum; kAhead of them are requested together (one at a time: 29.6 and
+// 32.5 us per launch on 250k FP32 nodes, so @ADJ@), and summed in their order.
+constexpr int kAhead = 4;
 
 // lamH_hat = lambda_H + C^T K mu ; tmpE = mu + gamma D^hv^T K mu
 template <typename T>
-__global__ void k_adj2(AA<T> a) {
+__global__ __launch_bounds__(256) void k_adj2(AA<T> a) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t t = g >> 6;
     if (t >= a.tiles) return;
-    const int l = (int)(g & 63);
     const int64_t j = g;
     const int w = a.twidth[t];
-    const int64_t base = a.toff[t] + l;
+    const int64_t base = a.toff[t] + (g & 63);
     T sx = 0, sy = 0, sh = 0;
-    for (int q = 0; q < w; ++q) {
+    int q = 0;
+    for (; q + kAhead <= w; q += kAhead) {
+        int32_t i[kAhead];
+        T wx[kAhead], wy[kAhead], wh[kAhead], km[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t e = base + (int64_t)(q + u) * 64;
+            i[u] = a.tsrc[e];
+            wx[u] = a.tw[e];
+            wy[u] = a.tw[a.tcap + e];
+            wh[u] = a.tw[2 * a.tcap + e];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) km[u] = a.kmu[i[u]];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            sx += wx[u] * km[u];
+            sy += wy[u] * km[u];
+            sh += wh[u] * km[u];
+        }
+    }
+    for (; q < w; ++q) {
         const int64_t e = base + (int64_t)q * 64;
-        const int32_t i = a.tsrc[e];
-        const T km = a.kmu[i];
+        const T km = a.kmu[a.tsrc[e]];
         sx += a.tw[e] * km;
         sy += a.tw[a.tcap + e] * km;
         sh += a.tw[2 * a.tcap + e] * km;
@@ -94,18 +143,43 @@ __global__ void k_adj2(AA<T> a) {
     a.tmpE[j] = a.mu[j] + (T)a.g * sh;
 }
 
-// lambda_E^n = tmpE + a (-D^dy^T lhx + D^dx^T lhy) ; lambda_H^n = lamH_hat + a gamma D^hv^T lamH_hat
+// lambda_E^n = tmpE + a (-D^dy^T lhx + D^dx^T lhy) + r^n ; lambda_H^n = lamH_hat +
+// a gamma D^hv^T lamH_hat ; with `terms` also the node terms of step n - 1, for
+// which E^n and E^{n-1} are at hand.
 template <typename T>
-__global__ void k_adj3(AA<T> a) {
+__global__ __launch_bounds__(256) void k_adj3(AA<T> a, int terms) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t t = g >> 6;
     if (t >= a.tiles) return;
-    const int l = (int)(g & 63);
     const int64_t j = g;
     const int w = a.twidth[t];
-    const int64_t base = a.toff[t] + l;
+    const int64_t base = a.toff[t] + (g & 63);
     T ce = 0, hx = 0, hy = 0;
-    for (int q = 0; q < w; ++q) {
+    int q = 0;
+    for (; q + kAhead <= w; q += kAhead) {
+        int32_t i[kAhead];
+        T wx[kAhead], wy[kAhead], wh[kAhead], lx[kAhead], ly[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t e = base + (int64_t)(q + u) * 64;
+            i[u] = a.tsrc[e];
+            wx[u] = a.tw[e];
+            wy[u] = a.tw[a.tcap + e];
+            wh[u] = a.tw[2 * a.tcap + e];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            lx[u] = a.lhat[(int64_t)i[u] * 2 + 0];
+            ly[u] = a.lhat[(int64_t)i[u] * 2 + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            ce += -wy[u] * lx[u] + wx[u] * ly[u];
+            hx += wh[u] * lx[u];
+            hy += wh[u] * ly[u];
+        }
+    }
+    for (; q < w; ++q) {
         const int64_t e = base + (int64_t)q * 64;
         const int32_t i = a.tsrc[e];
         const T lx = a.lhat[(int64_t)i * 2 + 0], ly = a.lhat[(int64_t)i * 2 + 1];
@@ -116,29 +190,37 @@ __global__ void k_adj3(AA<T> a) {
     }
     if (j >= a.N) return;
     const T A = (T)a.a, AG = (T)(a.a * a.g);
-    a.lamE_out[j] = a.tmpE[j] + A * ce;
+    T lam = a.tmpE[j] + A * ce;
+    for (int r = 0; r < a.n_rcv; ++r)
+        if (a.rnode[r] == (int32_t)j) lam += a.gtr[r];
+    a.lamE_out[j] = lam;
     a.lamH_out[j * 2 + 0] = a.lhat[j * 2 + 0] + AG * hx;
     a.lamH_out[j * 2 + 1] = a.lhat[j * 2 + 1] + AG * hy;
+    if (terms) node_terms(a, j, lam);
 }
 
-// sources: amplitude gradient and the s^{n+1} term of the eps_r gradient;
-// receivers: residual injection r^n (n >= 1).  One thread, fixed order.
+// More sources or receivers than the node loops look through: one thread, in
+// order.  Amplitude gradient and the s^{n+1} term of the eps_r gradient of step
+// n; receiver residual r^n (n >= 1).
+constexpr int kMaxFoldedSrc = 16, kMaxFoldedRcv = 64;
 template <typename T>
-__global__ void k_adj_src_rcv(int n, int S, const int32_t* snode, const T* samp, const T* swave, const T* mu,
-                              const void* eps_r, double* geps, double* gamp, int R, const int32_t* rnode,
-                              const T* gtr, T* lamE, const uint8_t* emask) {
+__global__ void k_adj_src(int S, const int32_t* snode, const T* samp, const T* swave, const T* mu, const void* eps_r,
+                          double* geps, double* gamp, const uint8_t* emask) {
     if (threadIdx.x || blockIdx.x) return;
     for (int s = 0; s < S; ++s) {
         const int64_t i = snode[s];
-        const double g = (double)swave[(int64_t)n * S + s];
+        const double g = (double)swave[s];
         gamp[s] += g * (double)mu[i];
         if (emask[i] & 1) {
             const double er = eps_r ? (sizeof(T) == 8 ? ((const double*)eps_r)[i] : (double)((const float*)eps_r)[i]) : 1.0;
             geps[i] += ((double)mu[i] / er) * ((double)samp[s] * g);
         }
     }
-    if (n >= 1)
-        for (int r = 0; r < R; ++r) lamE[rnode[r]] += gtr[(int64_t)(n - 1) * R + r];
+}
+template <typename T>
+__global__ void k_adj_rcv(int R, const int32_t* rnode, const T* gtr, T* lamE) {
+    if (threadIdx.x || blockIdx.x) return;
+    for (int r = 0; r < R; ++r) lamE[rnode[r]] += gtr[r];
 }
 
 template <typename T>
@@ -151,25 +233,6 @@ __global__ void k_adj_init(T* lamE, T* lamH, int64_t N, double* geps, double* ga
         geps[i] = 0.0;
     }
     if (i < S) gamp[i] = 0.0;
-}
-
-template <typename T>
-__global__ void k_adj_terminal(T* lamE, int R, const int32_t* rnode, const T* gtr, int T_) {
-    if (threadIdx.x || blockIdx.x) return;
-    for (int r = 0; r < R; ++r) lamE[rnode[r]] += gtr[(int64_t)(T_ - 1) * R + r];
-}
-
-__global__ void k_set_ctr(int32_t* c, int v) {
-    if (!threadIdx.x && !blockIdx.x) *c = v;
-}
-
-template <typename T>
-__global__ void k_src_fwd(T* E, const uint8_t* emask, int S, const int32_t* node, const T* amp, const T* wave, int n) {
-    if (threadIdx.x || blockIdx.x) return;
-    for (int s = 0; s < S; ++s) {
-        const int64_t i = node[s];
-        E[i] = (emask[i] & 1) ? E[i] + amp[s] * wave[(int64_t)n * S + s] : (T)0;
-    }
 }
 
 template <typename T>
@@ -189,7 +252,6 @@ int adjoint_impl(const rbffd_plan* p, const rbffd_fields* f, const rbffd_adjoint
     T* lamE[2] = {(T*)take(eb), (T*)take(eb)};
     T* lamH[2] = {(T*)take(hb), (T*)take(hb)};
     T* lhat = (T*)take(hb);
-    T* Ew[2] = {(T*)take(eb), (T*)take(eb)};
     T* Hw[2] = {(T*)take(hb), (T*)take(hb)};
     if (w - (char*)x->workspace > p->adj_ws_bytes) return set_err(p, RBFFD_ESIZE, "adjoint workspace too small");
     T* seg = (T*)x->seg_buf;
@@ -198,20 +260,17 @@ int adjoint_impl(const rbffd_plan* p, const rbffd_fields* f, const rbffd_adjoint
     const int nseg = (int)cdiv(T_, C);
     const int B = 256;
     const dim3 gN((unsigned)cdiv(N, B)), gT((unsigned)cdiv(o.tiles * 64, B));
+    const bool fold_src = x->n_src <= kMaxFoldedSrc, fold_rcv = x->n_rcv <= kMaxFoldedRcv;
+    const T* wave = (const T*)x->src_wave;
+    const T* gtr = (const T*)x->grad_traces;
 
     hipLaunchKernelGGL(k_adj_init<T>, gN, dim3(B), 0, st, lamE[0], lamH[0], N, x->grad_eps, x->grad_amp, x->n_src);
     if (x->n_src > (int64_t)gN.x * B) return set_err(p, RBFFD_ESIZE, "too many sources");
     if (x->n_rcv > 0)
-        hipLaunchKernelGGL(k_adj_terminal<T>, dim3(1), dim3(64), 0, st, lamE[0], x->n_rcv, x->rcv_node,
-                           (const T*)x->grad_traces, T_);
+        hipLaunchKernelGGL(k_adj_rcv<T>, dim3(1), dim3(64), 0, st, x->n_rcv, x->rcv_node,
+                           gtr + (int64_t)(T_ - 1) * x->n_rcv, lamE[0]);
     int cur = 0;
-
-    rbffd_fields wf{};
-    wf.E[0] = Ew[0];
-    wf.E[1] = Ew[1];
-    wf.H[0] = Hw[0];
-    wf.H[1] = Hw[1];
-    wf.eps_r = f ? f->eps_r : nullptr;
+    const void* eps_r = f ? f->eps_r : nullptr;
 
     AA<T> a{};
     a.N = N;
@@ -225,7 +284,7 @@ int adjoint_impl(const rbffd_plan* p, const rbffd_fields* f, const rbffd_adjoint
     a.g = p->gamma;
     a.dt = p->dt;
     a.eps0 = p->p.eps0;
-    a.eps_r = wf.eps_r;
+    a.eps_r = eps_r;
     a.emask = p->E.emask;
     a.mu = mu;
     a.kmu = kmu;
@@ -233,36 +292,50 @@ int adjoint_impl(const rbffd_plan* p, const rbffd_fields* f, const rbffd_adjoint
     a.tmpE = tmpE;
     a.geps = x->grad_eps;
 
+    a.snode = x->src_node;
+    a.samp = (const T*)x->src_amp;
+    a.gamp = x->grad_amp;
+    a.rnode = x->rcv_node;
+    a.n_src = fold_src ? x->n_src : 0;
+
     for (int k = nseg - 1; k >= 0; --k) {
         const int n0 = k * C, n1 = std::min(T_, n0 + C);
-        // restore checkpoint k and recompute E^{n0..n1}
+        // recompute E^{n0 + 1..n1} from checkpoint k; E^{n0} is read where it lies
         const char* slot = (const char*)x->ckpt + (int64_t)k * (eb + hb);
-        HIPCHK(p, hipMemcpyAsync(Ew[0], slot, eb, hipMemcpyDeviceToDevice, st));
+        auto En = [&](int n) { return n == n0 ? (const T*)slot : (const T*)(seg + (int64_t)(n - n0) * N); };
         HIPCHK(p, hipMemcpyAsync(Hw[0], slot + eb, hb, hipMemcpyDeviceToDevice, st));
-        HIPCHK(p, hipMemcpyAsync(seg, Ew[0], eb, hipMemcpyDeviceToDevice, st));
-        wf.cur = 0;
-        for (int n = n0; n < n1; ++n) {
-            int rc = rbffd_step(p, &wf, 1, st);
-            if (rc) return rc;
-            if (x->n_src > 0)
-                hipLaunchKernelGGL(k_src_fwd<T>, dim3(1), dim3(64), 0, st, (T*)wf.E[wf.cur], p->E.emask, x->n_src,
-                                   x->src_node, (const T*)x->src_amp, (const T*)x->src_wave, n);
-            HIPCHK(p, hipMemcpyAsync(seg + (int64_t)(n + 1 - n0) * N, wf.E[wf.cur], eb, hipMemcpyDeviceToDevice, st));
-        }
+        for (int n = n0; n < n1; ++n)
+            if (int rc = plain_step_into(p, En(n), Hw[(n - n0) & 1], (void*)En(n + 1), Hw[(n - n0 + 1) & 1], eps_r, x->n_src,
+                                         x->src_node, x->src_amp, wave + (int64_t)n * x->n_src, st))
+                return rc;
         // reverse sweep over the segment
         for (int n = n1 - 1; n >= n0; --n) {
             a.lamE = lamE[cur];
             a.lamH = lamH[cur];
             a.lamE_out = lamE[1 - cur];
             a.lamH_out = lamH[1 - cur];
-            a.En1 = seg + (int64_t)(n + 1 - n0) * N;
-            a.En = seg + (int64_t)(n - n0) * N;
-            hipLaunchKernelGGL(k_adj1<T>, gN, dim3(B), 0, st, a);
+            if (n == n1 - 1 || !fold_src || !fold_rcv) {   // else k_adj3 of step n + 1 has them
+                a.En1 = En(n + 1);
+                a.En = En(n);
+                a.swave = wave + (int64_t)n * x->n_src;
+                hipLaunchKernelGGL(k_adj1<T>, gN, dim3(B), 0, st, a);
+                if (!fold_src)
+                    hipLaunchKernelGGL(k_adj_src<T>, dim3(1), dim3(64), 0, st, x->n_src, x->src_node, a.samp, a.swave,
+                                       (const T*)mu, eps_r, x->grad_eps, x->grad_amp, p->E.emask);
+            }
             hipLaunchKernelGGL(k_adj2<T>, gT, dim3(B), 0, st, a);
-            hipLaunchKernelGGL(k_adj3<T>, gT, dim3(B), 0, st, a);
-            hipLaunchKernelGGL(k_adj_src_rcv<T>, dim3(1), dim3(64), 0, st, n, x->n_src, x->src_node,
-                               (const T*)x->src_amp, (const T*)x->src_wave, (const T*)mu, wf.eps_r, x->grad_eps,
-                               x->grad_amp, x->n_rcv, x->rcv_node, (const T*)x->grad_traces, lamE[1 - cur], p->E.emask);
+            const bool residual = n >= 1 && x->n_rcv > 0;
+            a.n_rcv = residual && fold_rcv ? x->n_rcv : 0;
+            a.gtr = residual ? gtr + (int64_t)(n - 1) * x->n_rcv : nullptr;
+            const int terms = n > n0 && fold_src && fold_rcv;
+            if (terms) {
+                a.En1 = En(n);
+                a.En = En(n - 1);
+                a.swave = wave + (int64_t)(n - 1) * x->n_src;
+            }
+            hipLaunchKernelGGL(k_adj3<T>, gT, dim3(B), 0, st, a, terms);
+            if (residual && !fold_rcv)
+                hipLaunchKernelGGL(k_adj_rcv<T>, dim3(1), dim3(64), 0, st, x->n_rcv, x->rcv_node, a.gtr, lamE[1 - cur]);
             cur = 1 - cur;
         }
     }

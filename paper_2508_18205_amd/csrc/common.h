@@ -155,6 +155,11 @@ inline RunWS run_ws(void* ws) {
     return w;
 }
 
+// one single-field step from (E, H) into (Eout, Hout) with the soft sources of
+// that step (wave: their waveform row), as a run computes it (step.hip)
+int plain_step_into(const rbffd_plan* p, const void* E, const void* H, void* Eout, void* Hout, const void* eps_r, int n_src,
+                    const int32_t* src_node, const void* src_amp, const void* wave, hipStream_t st);
+
 // K-field batch: per-field gamma from per-field constants c (device [K]), or
 // every field the plan's gamma when c is null (batched.hip)
 int fill_field_gamma(const rbffd_plan* p, const double* c_dev, hipStream_t st);

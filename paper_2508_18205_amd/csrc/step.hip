@@ -1997,9 +1997,25 @@ extern "C" int rbffd_half(const rbffd_plan* p, const rbffd_fields* f, int32_t wh
 
 namespace {
 template <typename TS>
-void launch_sources(const rbffd_plan* p, void* E, const rbffd_run_args* a, const void* wave, hipStream_t st) {
+void launch_sources(const rbffd_plan* p, void* E, int n_src, const int32_t* node, const void* amp, const void* wave,
+                    hipStream_t st) {
     hipLaunchKernelGGL(k_source<TS>, dim3(1), dim3(64), 0, st, (TS*)E, p->FE, p->dim == 2 ? 0 : 2, p->E.emask, p->E.nrm,
-                       a->n_src, a->src_node, a->src_amp, wave);
+                       n_src, node, amp, wave);
+}
+void sources(const rbffd_plan* p, void* E, int n_src, const int32_t* node, const void* amp, const void* wave, hipStream_t st) {
+    switch (p->p.fdtype) {
+        case RBFFD_F64: launch_sources<double>(p, E, n_src, node, amp, wave, st); break;
+        case RBFFD_F32: launch_sources<float>(p, E, n_src, node, amp, wave, st); break;
+        default: launch_sources<bf16s>(p, E, n_src, node, amp, wave, st);
+    }
+}
+// sources that the E update looks through by itself
+void fold_sources(HalfAux& x, int n_src, const int32_t* node, const void* amp, const void* wave) {
+    if (n_src <= 0 || n_src > kMaxFoldedSources) return;
+    x.n_src = n_src;
+    x.src = node;
+    x.samp = amp;
+    x.swave = wave;
 }
 template <typename TS>
 void launch_receivers(const rbffd_plan* p, const void* E, const rbffd_run_args* a, void* trace, hipStream_t st) {
@@ -2040,24 +2056,12 @@ void full_step(const rbffd_plan* p, const rbffd_fields* f, int c, int n, const r
         x.trace = (char*)a->traces + (int64_t)(n - 1) * a->n_rcv * tb;
     }
     const void* wave = (const char*)a->src_wave + ((int64_t)n + a->step0) * a->n_src * tb;
-    const bool folded = a->n_src > 0 && a->n_src <= kMaxFoldedSources;
-    if (folded) {
-        x.n_src = a->n_src;
-        x.src = a->src_node;
-        x.samp = a->src_amp;
-        x.swave = wave;
-    }
+    fold_sources(x, a->n_src, a->src_node, a->src_amp, wave);
     half(p, true, f->E[c], f->H[c], f->H[o], nullptr, st, x);
     if (a->energy_out && a->energy_every > 0 && n % a->energy_every == 0)
         energy(p, f->E[c], f->H[c], f->H[o], a->energy_out + n / a->energy_every, w, st);
     half(p, false, f->E[c], f->H[o], f->E[o], f->eps_r, st, x);
-    if (a->n_src > 0 && !folded) {
-        switch (p->p.fdtype) {
-            case RBFFD_F64: launch_sources<double>(p, f->E[o], a, wave, st); break;
-            case RBFFD_F32: launch_sources<float>(p, f->E[o], a, wave, st); break;
-            default: launch_sources<bf16s>(p, f->E[o], a, wave, st);
-        }
-    }
+    if (a->n_src > kMaxFoldedSources) sources(p, f->E[o], a->n_src, a->src_node, a->src_amp, wave, st);
     if (a->n_rcv > 0 && n == a->T - 1) {
         void* row = (char*)a->traces + (int64_t)n * a->n_rcv * tb;
         switch (p->p.fdtype) {
@@ -2076,6 +2080,17 @@ int plain_steps(const rbffd_run_args* a, int n) {
     return e - n;
 }
 }  // namespace
+
+int plain_step_into(const rbffd_plan* p, const void* E, const void* H, void* Eout, void* Hout, const void* eps_r, int n_src,
+                    const int32_t* src_node, const void* src_amp, const void* wave, hipStream_t st) {
+    HalfAux x;
+    fold_sources(x, n_src, src_node, src_amp, wave);
+    half(p, true, E, H, Hout, nullptr, st);
+    half(p, false, E, Hout, Eout, eps_r, st, x);
+    if (n_src > kMaxFoldedSources) sources(p, Eout, n_src, src_node, src_amp, wave, st);
+    HIPCHK(p, hipGetLastError());
+    return RBFFD_OK;
+}
 
 int batched_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_args* a, void* ws, hipStream_t st);
 

@@ -209,6 +209,16 @@ class Solver:
             er = self.to_internal(np.asarray(eps_r)[:, None], 1, dtype=self.cdtype).reshape(-1).contiguous()
         return State([E, torch.zeros_like(E)], [H, torch.zeros_like(H)], 0, er)
 
+    def state_at_rest(self, eps_r=None):
+        """Single-field state with zero fields; eps_r a tensor [N] in original order."""
+        n = self.NH if self.params.mode == 2 else self.N
+        E = [torch.zeros((self.N, self.FE), dtype=self.dtype, device=self.device) for _ in range(2)]
+        H = [torch.zeros((n, self.FH), dtype=self.dtype, device=self.device) for _ in range(2)]
+        er = None
+        if eps_r is not None:
+            er = self.permute(eps_r.detach().to(device=self.device, dtype=self.cdtype).reshape(-1, 1).contiguous()).reshape(-1)
+        return State(E, H, 0, er)
+
     def state_batched(self, E0b, H0b):
         """K-field state from original-order E0b [K, N, 1], H0b [K, N, 2] -> [N, F, K]."""
         K = E0b.shape[0]
@@ -328,6 +338,11 @@ class Solver:
 
     def adjoint(self, st_eps, T, ckpt, ckpt_every, grad_traces, src=None, rcv=None):
         """Gradients (grad_eps [N] original order, grad_amp [S]) of J(traces)."""
+        g, gamp = self.adjoint_device(st_eps, T, ckpt, ckpt_every, grad_traces, src, rcv)
+        return g.cpu().numpy(), (gamp.cpu().numpy() if gamp is not None else None)
+
+    def adjoint_device(self, st_eps, T, ckpt, ckpt_every, grad_traces, src=None, rcv=None):
+        """``adjoint`` with the gradients as FP64 tensors on the device."""
         a = _abi.AdjointArgs()
         a.T, a.ckpt_every, a.ckpt = int(T), int(ckpt_every), ckpt.data_ptr()
         keep = []
@@ -346,14 +361,13 @@ class Solver:
             gtr = torch.as_tensor(grad_traces).to(device=self.device, dtype=self.cdtype).contiguous()
             keep += [rn, gtr]
             a.n_rcv, a.rcv_node, a.grad_traces = len(rcv), rn.data_ptr(), gtr.data_ptr()
-        geps = torch.zeros(self.N, dtype=torch.float64, device=self.device)
+        geps = torch.empty(self.N, dtype=torch.float64, device=self.device)
         seg = torch.empty((ckpt_every + 1) * self.sizes.e_bytes, dtype=torch.uint8, device=self.device)
         aws = torch.empty(self.sizes.adjoint_ws_bytes, dtype=torch.uint8, device=self.device)
         a.grad_eps, a.seg_buf, a.workspace = geps.data_ptr(), seg.data_ptr(), aws.data_ptr()
         f = st_eps.struct()
         check(self.lib.rbffd_adjoint(self.plan, C.byref(f), C.byref(a), self.stream()), self.plan, "rbffd_adjoint")
-        g = self.permute(geps.reshape(-1, 1), 0, False).reshape(-1)
-        return g.cpu().numpy(), (gamp.cpu().numpy() if gamp is not None else None)
+        return self.permute(geps.reshape(-1, 1), 0, False).reshape(-1), gamp
 
     # ---- diagnostics -------------------------------------------------------------------
     def energy(self, E, Ha, Hb):
