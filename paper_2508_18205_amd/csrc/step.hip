@@ -88,8 +88,13 @@ __device__ __forceinline__ void record_receivers(const A& a, int64_t g) {
 }
 
 // Soft sources: E at node i after the bracket gains amp * wave for every
-// source on it, in source order, each sum rounded to the storage type as a
-// store would; PEC nodes stay 0.
+// source on it, in source order, the product rounded before the sum and each
+// sum rounded to the storage type as a store would; PEC nodes stay 0.
+template <typename TC>
+__device__ __forceinline__ TC source_term(const void* amp, const void* wave, int s) {
+#pragma clang fp contract(off)
+    return ((const TC*)amp)[s] * ((const TC*)wave)[s];
+}
 template <typename TS, typename TW, typename A>
 __device__ __forceinline__ typename Store<TS>::C sourced(const A& a, int64_t i, bool free_, typename Store<TS>::C v) {
     using TC = typename Store<TS>::C;
@@ -97,7 +102,7 @@ __device__ __forceinline__ typename Store<TS>::C sourced(const A& a, int64_t i, 
     if constexpr (A::kAux)
         for (int s = 0; s < a.n_src; ++s)
             if (a.src[s] == (int32_t)i)
-                v = Store<TS>::rnd(Store<TS>::rnd(v) + ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s]);
+                v = Store<TS>::rnd(Store<TS>::rnd(v) + source_term<TC>(a.samp, a.swave, s));
     return v;
 }
 // 3D: the source acts on Ez; on a curved wall (mask bit 3) E is already
@@ -110,7 +115,7 @@ __device__ __forceinline__ void sourced3(const A& a, int64_t i, uint8_t m, typen
     if constexpr (A::kAux)
         for (int s = 0; s < a.n_src; ++s) {
             if (a.src[s] != (int32_t)i) continue;
-            const TC v = ((const TC*)a.samp)[s] * ((const TC*)a.swave)[s];
+            const TC v = source_term<TC>(a.samp, a.swave, s);
             if (m & 8) {
                 const double* n = a.wnrm + 3 * i;
                 x = S::rnd(S::rnd(x) + v * (TC)n[2] * (TC)n[0]);
@@ -1642,7 +1647,7 @@ __global__ void k_source(TS* E, int FE, int comp, const uint8_t* emask, const do
     for (int s = 0; s < S; ++s) {
         const int64_t i = node[s];
         const int64_t e = i * FE + comp;
-        const TC v = ((const TC*)amp)[s] * ((const TC*)wave)[s];
+        const TC v = source_term<TC>(amp, wave, s);
         if (emask[i] & 8) {
             // curved 3D wall: E is already projected on the normal n, so adding
             // the projected source v n_comp n keeps (E + v e_comp) projected

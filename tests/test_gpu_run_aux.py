@@ -70,6 +70,22 @@ def test_run_auxiliaries(dim, precision, T, S, R, lds):
         assert torch.equal(got[s.sizes.e_bytes:], a.H.contiguous().view(-1).view(torch.uint8))
 
 
+@pytest.mark.parametrize("dim,precision,lds", [(2, "f32", 0), (2, "f32", 1), (2, "f32", 3), (2, "bf16", 1), (2, "f64", 3),
+                                               (3, "f32", 0), (3, "f32", 1), (3, "f32", 3), (3, "f64", 2)])
+def test_folded_sources_equal_separate(dim, precision, lds):
+    # silent sources on far nodes make them 17: the same terms, added by a kernel of their own
+    w = _workload(dim, 9, 5, 1)
+    s = Solver.from_workload(w, precision=precision)
+    s.set_variant(block=256, xcd=1, lds=lds)
+    out = []
+    for pad in (0, 12):
+        st = s.state(w.E0, w.H0)
+        s.run(st, 9, src=(np.r_[w.src_node, np.zeros(pad, int)], np.r_[w.src_amp, np.zeros(pad)],
+                          np.c_[w.src_wave, np.zeros((9, pad))]))
+        out.append((st.E.clone(), st.H.clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("K", [4, 24, 64, 80])
 def test_batch_energy_samples(K):
     """Per-field energies of a batch at odd widths against the sum of eq. 20 over the stored fields."""
