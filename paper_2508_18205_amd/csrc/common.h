@@ -24,6 +24,25 @@
 #define RBFFD_SMALL 65536         // node counts up to which single-field plans do not
 #define RBFFD_SMALL_2D 80000      // start on the staged kernels (plan.hip)
 #define RBFFD_SMALL_3D_F32 24576
+// Operators (weights, positions) up to this size stay in the 256 MB memory-side
+// cache between half steps, below 32 MB in the L2s, when loaded ordinarily; larger
+// ones stream through it.  us per step, non-temporal / ordinary loads: 2D FP32 68k
+// nodes (n 12, 19 MB) 17.1 / 11.0, 490k (n 25, 188 MB) 65.0 / 60.0, 1M (384 MB) 132 /
+// 149; 2D FP64 250k (176 MB) 60.8 / 56.5, 490k (345 MB) 119 / 133; 3D FP32 125k (117
+// MB) 53.6 / 46.7, 262k (245 MB) 79.6 / 74.7.  The exception: 2D operators of at most
+// RBFFD_BAND_NODE bytes per node between these two sizes, too large for the L2s and
+// with little to sum per byte: 160k nodes (n 25 FP32, 61 MB) 22.5 / 23.6, 123k (n 12
+// FP64, 63 MB) 23.7 / 24.9, at 46 MB 20.2 / 19.8 and at 96 MB 33.1 / 32.6.
+// 2D FP32 and BF16 sets below RBFFD_CACHED_F32 nodes keep the streaming loads too:
+// there the tuner's usual choice is the small-set kernels (12 to 27 us at 90k nodes,
+// staged 18 to 29), which sum in another order, and a tuned plan's results are to
+// follow from its size, not from a race between the two (staged with ordinary loads
+// would take 12.7 to 25; from 115k nodes on staged wins either way).
+#define RBFFD_CACHED_BYTES ((int64_t)256 << 20)
+#define RBFFD_BAND_LO ((int64_t)44 << 20)
+#define RBFFD_BAND_HI ((int64_t)76 << 20)
+#define RBFFD_BAND_NODE 512
+#define RBFFD_CACHED_F32 120000
 #define RBFFD_KSLICE 16           // widest field slice of the staged K-field batch
 #define RBFFD_LDS_BUDGET_BATCH 122880
 #define RBFFD_LDS_CU 163840       // LDS of one CU (gfx950)
@@ -238,4 +257,12 @@ int replay_steps(const rbffd_plan* p, int T, int cur, hipStream_t st, Rec rec, i
 __device__ __forceinline__ int xcd_remap(int b, int nb) {
     const int x = b & 7, q = nb >> 3, r = nb & 7;
     return x * q + (x < r ? x : r) + (b >> 3);
+}
+// The same tiles, each XCD's in reverse: the E update of a staged step starts with
+// what the H update read last and still finds it in cache (90k FP32 nodes, n 12,
+// 13.3 -> 12.7 us per step; larger sets gain nothing and lose nothing).
+__device__ __forceinline__ int tile_back(int xcd) {
+    const int b = blockIdx.x, nb = gridDim.x, x = b & 7, q = nb >> 3, r = nb & 7;
+    const int back = ((q + (x < r ? 1 : 0) - 1 - (b >> 3)) << 3) | x;
+    return xcd ? xcd_remap(back, nb) : back;
 }

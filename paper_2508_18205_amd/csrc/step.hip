@@ -33,6 +33,7 @@ namespace {
 template <typename TS, typename TW>
 struct SA {
     static constexpr bool kAux = false;
+    static constexpr bool kStream = true;   // staged kernels: weights and positions loaded non-temporally
     const TS* E;          // E^n
     const TS* H;          // H update: H^n ; E update: H^{n+1}
     const int32_t* hoff;  // LDS staging: halo lists
@@ -72,6 +73,15 @@ struct SX : SA<TS, TW> {
     const int32_t* src;
     const void* samp;     // [n_src] amplitudes, [n_src] waveform row (TC)
     const void* swave;
+};
+
+// The same arguments for an operator that stays in the memory-side cache from
+// one half step to the next: its loads are ordinary ones, which are kept there.
+// Non-temporal loads are the better ones for what streams from HBM.
+template <typename B>
+struct Cached : B {
+    static constexpr bool kStream = false;
+    explicit Cached(const B& b) : B(b) {}
 };
 
 // Receivers: the H update of step n + 1 reads E^{n+1} anyway, so the lanes of
@@ -1057,27 +1067,38 @@ __device__ __forceinline__ void copy4(TW (&d)[4], const TW (&s)[4]) {
     d[2] = s[2];
     d[3] = s[3];
 }
+// streamed (non-temporal) or cached loads of a chunk's weights and positions
+template <bool STREAM, typename TW, typename WV>
+__device__ __forceinline__ void ldw(const TW* p, WV (&w)[4]) {
+    if constexpr (STREAM) WF<TW>::ld(p, w);
+    else WF<TW>::ldp(p, w);
+}
+template <bool STREAM>
+__device__ __forceinline__ uint4 ldpos(const uint4* p) {
+    if constexpr (STREAM) return ldu4s(p);
+    else return *p;
+}
 // weights of chunk q of a 2D block (left unchanged past the chunk counts)
-template <typename TW, typename WV = typename WF<TW>::V>
+template <bool STREAM, typename TW, typename WV = typename WF<TW>::V>
 __device__ __forceinline__ void load2(const TW* pc, const TW* ph, int q, int C4, int V4, WV (&x)[4], WV (&y)[4],
                                       WV (&h)[4]) {
     if (q < C4) {
-        WF<TW>::ld(pc + (q * 2 + 0) * WF<TW>::CH, x);
-        WF<TW>::ld(pc + (q * 2 + 1) * WF<TW>::CH, y);
+        ldw<STREAM>(pc + (q * 2 + 0) * WF<TW>::CH, x);
+        ldw<STREAM>(pc + (q * 2 + 1) * WF<TW>::CH, y);
     }
-    if (q < V4) WF<TW>::ld(ph + q * WF<TW>::CH, h);
+    if (q < V4) ldw<STREAM>(ph + q * WF<TW>::CH, h);
 }
 
 // weights of chunk q of a 3D block (left unchanged past the chunk counts)
-template <typename TW>
+template <bool STREAM, typename TW>
 __device__ __forceinline__ void load3(const TW* pc, const TW* ph, int q, int C4, int V4, TW (&x)[4], TW (&y)[4],
                                       TW (&z)[4], TW (&h)[4]) {
     if (q < C4) {
-        ldw4(pc + (q * 3 + 0) * RBFFD_TILE * 4, x);
-        ldw4(pc + (q * 3 + 1) * RBFFD_TILE * 4, y);
-        ldw4(pc + (q * 3 + 2) * RBFFD_TILE * 4, z);
+        ldw<STREAM>(pc + (q * 3 + 0) * RBFFD_TILE * 4, x);
+        ldw<STREAM>(pc + (q * 3 + 1) * RBFFD_TILE * 4, y);
+        ldw<STREAM>(pc + (q * 3 + 2) * RBFFD_TILE * 4, z);
     }
-    if (q < V4) ldw4(ph + q * RBFFD_TILE * 4, h);
+    if (q < V4) ldw<STREAM>(ph + q * RBFFD_TILE * 4, h);
 }
 
 // 3-vector LDS entries, packed (12 B in FP32) so that more workgroups fit
@@ -1200,16 +1221,16 @@ __global__ __launch_bounds__(256) void k_h2l(A a) {
     const TW* ph = a.wh + tile * a.V4 * WF<TW>::CH + lane * WF<TW>::LS;
     const int qm = max(a.C4, a.V4);
     // chunk q + 1 is loaded while chunk q is summed
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<A::kStream>(pl);
     WV nx[4] = {0, 0, 0, 0}, ny[4] = {0, 0, 0, 0}, nh[4] = {0, 0, 0, 0};
-    load2(pc, ph, 0, a.C4, a.V4, nx, ny, nh);
+    load2<A::kStream>(pc, ph, 0, a.C4, a.V4, nx, ny, nh);
     for (int q = 0; q < qm; ++q) {
         const uint4 lc = li;
         WV wx[4], wy[4], wh[4];
         copy4(wx, nx); copy4(wy, ny); copy4(wh, nh);
         if (q + 1 < qm) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load2(pc, ph, q + 1, a.C4, a.V4, nx, ny, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<A::kStream>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load2<A::kStream>(pc, ph, q + 1, a.C4, a.V4, nx, ny, nh);
         }
         const int hf = q & 1;
         if (q < a.C4) {
@@ -1255,7 +1276,7 @@ __global__ __launch_bounds__(256) void k_e2l(A a) {
     using WV = typename WF<TW>::V;
     TC* sE = lds_base<TC>();
     TC* sH = sE + ((a.hmax + 3) & ~3);
-    const int wg = a.xcd ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int wg = tile_back(a.xcd);
     const int h0 = a.hoff[wg], hc = a.hoff[wg + 1] - h0;
     stage_rounds<4, Val3<TC>>(
         a.hpool + h0, hc,
@@ -1283,16 +1304,16 @@ __global__ __launch_bounds__(256) void k_e2l(A a) {
     const TW* pc = a.wc + tile * a.C4 * 2 * WF<TW>::CH + lane * WF<TW>::LS;
     const TW* ph = a.wh + tile * a.V4 * WF<TW>::CH + lane * WF<TW>::LS;
     const int qm = max(a.C4, a.V4);
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<A::kStream>(pl);
     WV nx[4] = {0, 0, 0, 0}, ny[4] = {0, 0, 0, 0}, nh[4] = {0, 0, 0, 0};
-    load2(pc, ph, 0, a.C4, a.V4, nx, ny, nh);
+    load2<A::kStream>(pc, ph, 0, a.C4, a.V4, nx, ny, nh);
     for (int q = 0; q < qm; ++q) {
         const uint4 lc = li;
         WV wx[4], wy[4], wh[4];
         copy4(wx, nx); copy4(wy, ny); copy4(wh, nh);
         if (q + 1 < qm) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load2(pc, ph, q + 1, a.C4, a.V4, nx, ny, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<A::kStream>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load2<A::kStream>(pc, ph, q + 1, a.C4, a.V4, nx, ny, nh);
         }
         const int hf = q & 1;
         if (q < a.C4) {
@@ -1351,16 +1372,16 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3l(A a) {
     const TW* ph = a.wh + tile * a.V4 * RBFFD_TILE * 4 + lane * WChunk<TW>::LS;
     const int qm = max(a.C4, a.V4);
     // chunk q + 1 is loaded while chunk q is summed
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<A::kStream>(pl);
     TW nx[4] = {0, 0, 0, 0}, ny[4] = {0, 0, 0, 0}, nz[4] = {0, 0, 0, 0}, nh[4] = {0, 0, 0, 0};
-    load3(pc, ph, 0, a.C4, a.V4, nx, ny, nz, nh);
+    load3<A::kStream>(pc, ph, 0, a.C4, a.V4, nx, ny, nz, nh);
     for (int q = 0; q < qm; ++q) {
         const uint4 lc = li;
         TW wx[4], wy[4], wz[4], wh[4];
         copy4(wx, nx); copy4(wy, ny); copy4(wz, nz); copy4(wh, nh);
         if (q + 1 < qm) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load3(pc, ph, q + 1, a.C4, a.V4, nx, ny, nz, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<A::kStream>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load3<A::kStream>(pc, ph, q + 1, a.C4, a.V4, nx, ny, nz, nh);
         }
         const int hf = q & 1;
         if (q < a.C4) {
@@ -1400,7 +1421,7 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(A a) {
     using TC = typename S::C;
     TC* sE = lds_base<TC>();
     TC* sH = sE + 3 * (int64_t)a.hmax;
-    const int wg = a.xcd ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int wg = tile_back(a.xcd);
     const int h0 = a.hoff[wg], hc = a.hoff[wg + 1] - h0;
     stage_rounds<4, Val6<TC>>(
         a.hpool + h0, hc,
@@ -1429,16 +1450,16 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3l(A a) {
     const TW* pc = a.wc + tile * a.C4 * 3 * RBFFD_TILE * 4 + lane * WChunk<TW>::LS;
     const TW* ph = a.wh + tile * a.V4 * RBFFD_TILE * 4 + lane * WChunk<TW>::LS;
     const int qm = max(a.C4, a.V4);
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<A::kStream>(pl);
     TW nx[4] = {0, 0, 0, 0}, ny[4] = {0, 0, 0, 0}, nz[4] = {0, 0, 0, 0}, nh[4] = {0, 0, 0, 0};
-    load3(pc, ph, 0, a.C4, a.V4, nx, ny, nz, nh);
+    load3<A::kStream>(pc, ph, 0, a.C4, a.V4, nx, ny, nz, nh);
     for (int q = 0; q < qm; ++q) {
         const uint4 lc = li;
         TW wx[4], wy[4], wz[4], wh[4];
         copy4(wx, nx); copy4(wy, ny); copy4(wz, nz); copy4(wh, nh);
         if (q + 1 < qm) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load3(pc, ph, q + 1, a.C4, a.V4, nx, ny, nz, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<A::kStream>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load3<A::kStream>(pc, ph, q + 1, a.C4, a.V4, nx, ny, nz, nh);
         }
         const int hf = q & 1;
         if (q < a.C4) {
@@ -1504,19 +1525,19 @@ __device__ __forceinline__ void stage_vec3(const TS* F, const int32_t* list, int
 // curl sums over the curl slots: d_x, d_y, d_z of the staged 3-vector field
 // (reference values f0) into the six accumulators c[0..5] =
 // (x f_y, x f_z, y f_x, y f_z, z f_x, z f_y)
-template <typename TC, typename TW>
+template <bool STREAM, typename TC, typename TW>
 __device__ __forceinline__ void curl_sums3(const TC* sF, const uint4* pl, const TW* pc, int C4, const TC (&f0)[3],
                                            TC (&c)[6]) {
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<STREAM>(pl);
     TW nx[4] = {0, 0, 0, 0}, ny[4] = {0, 0, 0, 0}, nz[4] = {0, 0, 0, 0}, nh[4];
-    load3(pc, (const TW*)nullptr, 0, C4, 0, nx, ny, nz, nh);
+    load3<STREAM>(pc, (const TW*)nullptr, 0, C4, 0, nx, ny, nz, nh);
     for (int q = 0; q < C4; ++q) {
         const uint4 lc = li;
         TW wx[4], wy[4], wz[4];
         copy4(wx, nx); copy4(wy, ny); copy4(wz, nz);
         if (q + 1 < C4) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load3(pc, (const TW*)nullptr, q + 1, C4, 0, nx, ny, nz, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<STREAM>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load3<STREAM>(pc, (const TW*)nullptr, q + 1, C4, 0, nx, ny, nz, nh);
         }
         const int hf = q & 1;
 #pragma unroll
@@ -1532,19 +1553,19 @@ __device__ __forceinline__ void curl_sums3(const TC* sF, const uint4* pl, const 
 }
 
 // hyperviscosity sums over the HV slots of the staged 3-vector field
-template <typename TC, typename TW>
+template <bool STREAM, typename TC, typename TW>
 __device__ __forceinline__ void hv_sums3(const TC* sF, const uint4* pl, const TW* ph, int V4, const TC (&f0)[3],
                                          TC (&v3)[3]) {
-    uint4 li = ldu4s(pl);
+    uint4 li = ldpos<STREAM>(pl);
     TW nx[4], ny[4], nz[4], nh[4] = {0, 0, 0, 0};
-    load3((const TW*)nullptr, ph, 0, 0, V4, nx, ny, nz, nh);
+    load3<STREAM>((const TW*)nullptr, ph, 0, 0, V4, nx, ny, nz, nh);
     for (int q = 0; q < V4; ++q) {
         const uint4 lc = li;
         TW wh[4];
         copy4(wh, nh);
         if (q + 1 < V4) {
-            if (((q + 1) & 1) == 0) li = ldu4s(pl + ((q + 1) >> 1) * RBFFD_TILE);
-            load3((const TW*)nullptr, ph, q + 1, 0, V4, nx, ny, nz, nh);
+            if (((q + 1) & 1) == 0) li = ldpos<STREAM>(pl + ((q + 1) >> 1) * RBFFD_TILE);
+            load3<STREAM>((const TW*)nullptr, ph, q + 1, 0, V4, nx, ny, nz, nh);
         }
         const int hf = q & 1;
 #pragma unroll
@@ -1580,11 +1601,11 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_h3p(A a) {
     const TW* ph = a.wh + tl * a.V4 * RBFFD_TILE * 4 + lane * WChunk<TW>::LS;
     stage_vec3<TS>(a.E, a.hpool + h0, hc, sF);
     __syncthreads();
-    if (live) curl_sums3<TC, TW>(sF, pl, pc, a.C4, e0, c);
+    if (live) curl_sums3<A::kStream, TC, TW>(sF, pl, pc, a.C4, e0, c);
     __syncthreads();
     stage_vec3<TS>(a.H, a.hpool + h0, hc, sF);
     __syncthreads();
-    if (live) hv_sums3<TC, TW>(sF, pl, ph, a.V4, h0v, v);
+    if (live) hv_sums3<A::kStream, TC, TW>(sF, pl, ph, a.V4, h0v, v);
     if (live) record_receivers<TS, TW>(a, i);
     if (live && i < a.N) {
         const TC F = (TC)a.a, G = (TC)a.g;
@@ -1599,7 +1620,7 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(A a) {
     using S = Store<TS>;
     using TC = typename S::C;
     TC* sF = lds_base<TC>();
-    const int wg = a.xcd ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int wg = tile_back(a.xcd);
     const int h0 = a.hoff[wg], hc = a.hoff[wg + 1] - h0;
     const int64_t tile = (int64_t)wg * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const bool live = tile < a.tiles;
@@ -1616,11 +1637,11 @@ __global__ __launch_bounds__(RBFFD_WGT_3D_F32) void k_e3p(A a) {
     const TW* ph = a.wh + tl * a.V4 * RBFFD_TILE * 4 + lane * WChunk<TW>::LS;
     stage_vec3<TS>(a.H, a.hpool + h0, hc, sF);
     __syncthreads();
-    if (live) curl_sums3<TC, TW>(sF, pl, pc, a.C4, h0v, c);
+    if (live) curl_sums3<A::kStream, TC, TW>(sF, pl, pc, a.C4, h0v, c);
     __syncthreads();
     stage_vec3<TS>(a.E, a.hpool + h0, hc, sF);
     __syncthreads();
-    if (live) hv_sums3<TC, TW>(sF, pl, ph, a.V4, e0, v);
+    if (live) hv_sums3<A::kStream, TC, TW>(sF, pl, ph, a.V4, e0, v);
     if (live && i < a.N) {
         const TC k = kappa_of(a, i), G = (TC)a.g;
         // c = (xHy, xHz, yHx, yHz, zHx, zHy)
@@ -1808,6 +1829,16 @@ bool small_set(const rbffd_plan* p, const OpBlock& o) {
     return p->dim == 2 || p->p.fdtype == RBFFD_F64 || small3_lds(o) <= RBFFD_LDS_CU;
 }
 
+// whether the operator of a staged half step (weights and positions) streams from
+// memory rather than staying in cache (RBFFD_CACHED_BYTES)
+bool streams(const rbffd_plan* p, const OpBlock& o) {
+    const int64_t node = (int64_t)(o.C4 * p->dim + o.V4) * chunk_bytes(p->p.wdtype) + o.Q8 * 16;
+    const int64_t bytes = o.tiles * RBFFD_TILE * node;
+    if (p->dim == 2 && p->p.fdtype != RBFFD_F64 && o.Nt < RBFFD_CACHED_F32) return true;
+    if (p->dim == 2 && node <= RBFFD_BAND_NODE && bytes > RBFFD_BAND_LO && bytes < RBFFD_BAND_HI) return true;
+    return bytes > RBFFD_CACHED_BYTES;
+}
+
 // what a run folds into one half step (null pointers: nothing)
 struct HalfAux {
     const int32_t* rcv = nullptr;   // H update
@@ -1818,11 +1849,21 @@ struct HalfAux {
     int n_rcv = 0, n_src = 0;
 };
 
-// kernel K with the auxiliaries of a run when this half step has any
+// kernel K with the auxiliaries of a run when this half step has any; staged
+// kernels also by whether the operator streams or stays cached
 #define RBFFD_LAUNCH_HALF(K, grid, block, lds)                                                              \
     do {                                                                                                    \
         if (aux) hipLaunchKernelGGL((K<TS, TW, SX<TS, TW>>), grid, block, lds, st, a);                       \
         else hipLaunchKernelGGL((K<TS, TW, SA<TS, TW>>), grid, block, lds, st, (const SA<TS, TW>&)a);        \
+    } while (0)
+
+#define RBFFD_LAUNCH_STAGED(K, grid, block, lds)                                                            \
+    do {                                                                                                    \
+        using SAt = SA<TS, TW>;                                                                             \
+        using SXt = SX<TS, TW>;                                                                             \
+        if (stream) RBFFD_LAUNCH_HALF(K, grid, block, lds);                                                 \
+        else if (aux) hipLaunchKernelGGL((K<TS, TW, Cached<SXt>>), grid, block, lds, st, Cached<SXt>(a));     \
+        else hipLaunchKernelGGL((K<TS, TW, Cached<SAt>>), grid, block, lds, st, Cached<SAt>((const SAt&)a));  \
     } while (0)
 
 template <typename TS, typename TW>
@@ -1880,11 +1921,12 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
     }
     if (p->collocated && o.hmax > 0 && p->var.lds) {
         using TC = typename Store<TS>::C;
+        const bool stream = streams(p, o);
         const dim3 grid((unsigned)o.nwg), block(o.wgt);
         if (p->dim == 2) {
             const size_t lds = (size_t)(((o.hmax + 3) & ~3) + 2 * o.hmax) * sizeof(TC);
-            if (hupd) RBFFD_LAUNCH_HALF(k_h2l, grid, block, lds);
-            else RBFFD_LAUNCH_HALF(k_e2l, grid, block, lds);
+            if (hupd) RBFFD_LAUNCH_STAGED(k_h2l, grid, block, lds);
+            else RBFFD_LAUNCH_STAGED(k_e2l, grid, block, lds);
             return;
         }
         if constexpr (kW22) {
@@ -1892,12 +1934,12 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
             return;
         } else if (o.stage == 1 && p->var.lds != 2) {
             const size_t lds = (size_t)6 * o.hmax * sizeof(TC);
-            if (hupd) RBFFD_LAUNCH_HALF(k_h3l, grid, block, lds);
-            else RBFFD_LAUNCH_HALF(k_e3l, grid, block, lds);
+            if (hupd) RBFFD_LAUNCH_STAGED(k_h3l, grid, block, lds);
+            else RBFFD_LAUNCH_STAGED(k_e3l, grid, block, lds);
         } else {
             const size_t lds = (size_t)3 * o.hmax * sizeof(TC);
-            if (hupd) RBFFD_LAUNCH_HALF(k_h3p, grid, block, lds);
-            else RBFFD_LAUNCH_HALF(k_e3p, grid, block, lds);
+            if (hupd) RBFFD_LAUNCH_STAGED(k_h3p, grid, block, lds);
+            else RBFFD_LAUNCH_STAGED(k_e3p, grid, block, lds);
         }
         return;
     }
@@ -1920,6 +1962,7 @@ void launch_half(const rbffd_plan* p, bool hupd, const void* E, const void* H, v
 }
 
 #undef RBFFD_LAUNCH_HALF
+#undef RBFFD_LAUNCH_STAGED
 
 void half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* out, const void* eps_r, hipStream_t st,
           const HalfAux& x = HalfAux()) {
