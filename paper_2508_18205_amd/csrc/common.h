@@ -43,6 +43,13 @@
 #define RBFFD_BAND_HI ((int64_t)76 << 20)
 #define RBFFD_BAND_NODE 512
 #define RBFFD_CACHED_F32 120000
+// Whole steps (step.hip): most tiles (their flags lie in the run workspace), how long
+// a workgroup waits for its neighbours' H before it computes it itself (ticks of 10
+// ns; the waits seen are below 10 us), and how many places ahead in the order of
+// dispatch a tile may look: a third to a half of the workgroups a chip holds
+#define RBFFD_STEP_TILES 16384
+#define RBFFD_STEP_PATIENCE 5000
+#define RBFFD_STEP_AHEAD 256
 #define RBFFD_KSLICE 16           // widest field slice of the staged K-field batch
 #define RBFFD_LDS_BUDGET_BATCH 122880
 #define RBFFD_LDS_CU 163840       // LDS of one CU (gfx950)
@@ -88,6 +95,12 @@ struct OpBlock {
     uint16_t* lself = nullptr;     // [tiles * 64] each node's own position (K-field batch)
     int32_t* hpool = nullptr;      // concatenated halo lists
     int32_t* hoff = nullptr;       // [nwg + 1] start of each workgroup's list
+    // whole steps (2D, single field): what each workgroup does, in order of dispatch.
+    // Tiles whose halo reaches far in that order come twice: their H update first of
+    // all, their E update last.  [2 nwg] (tile, kOnlyH or kOnlyE or 0, start and
+    // length of the halo list), then the count of those tiles
+    int4* ord = nullptr;
+    int32_t split = 0;             // that count on the host
     int32_t Q8 = 0;
     int64_t nwg = 0;
     int32_t wgt = RBFFD_WGT;       // nodes per staged workgroup tile (halo lists)
@@ -102,6 +115,8 @@ struct OpBlock {
     void* t_w = nullptr;           // [entries][4] (wx, wy, wh, 0) in weight precision
     int64_t t_cap = 0;             // entry capacity
 };
+
+constexpr int32_t kOnlyH = 1, kOnlyE = 2;   // OpBlock::ord
 
 struct NodeSet {
     int64_t N = 0;
@@ -163,14 +178,23 @@ inline bool has_wall_normals(const rbffd_plan* p) {
     return p->p.bc == RBFFD_BC_PEC && (p->p.pol == RBFFD_POL_TE || p->dim == 3);
 }
 
+// plans with a kernel that takes a whole step (step.hip): it keeps the order of its
+// tiles in OpBlock::ord
+inline bool can_step_whole(const rbffd_plan* p) {
+    return p->K == 1 && p->dim == 2 && p->collocated && p->p.pol != RBFFD_POL_TE && p->p.fdtype == RBFFD_F32 &&
+           p->p.wdtype == RBFFD_F32;
+}
+
 // ---- run workspace: FP64 reduction partials ---------------------------------
 constexpr int RED_BLOCKS = 1024;
 struct RunWS {
     double* part;       // [RED_BLOCKS * 12]
+    uint64_t* flags;    // [RBFFD_STEP_TILES] whole steps: the run and step each tile's H is at
 };
-inline RunWS run_ws(void* ws) {
+inline RunWS run_ws(void* ws) {   // fits the smallest workspace (1 MB)
     RunWS w;
     w.part = (double*)ws;
+    w.flags = (uint64_t*)(w.part + RED_BLOCKS * 12);
     return w;
 }
 

@@ -83,7 +83,7 @@ void layout_set(Bump& b, NodeSet& S, int dim, bool is_e, bool normals) {
     S.nrm = normals ? b.take<double>(S.N * dim) : nullptr;
 }
 
-void layout_block(Bump& b, OpBlock& o, int dim, int wb, int cb, int K, bool adjoint) {
+void layout_block(Bump& b, OpBlock& o, int dim, int wb, int cb, int K, bool adjoint, bool whole) {
     o.tiles = cdiv(o.Nt, RBFFD_TILE);
     o.C4 = (int)cdiv(o.n - 1, 4);
     o.V4 = o.nh > 0 ? (int)cdiv(o.nh - 1, 4) : 0;
@@ -102,6 +102,7 @@ void layout_block(Bump& b, OpBlock& o, int dim, int wb, int cb, int K, bool adjo
         if (K > 1) o.lself = b.take<uint16_t>(T);
         o.hpool = b.take<int32_t>(o.Nt * o.ns);
         o.hoff = b.take<int32_t>(o.nwg + 1);
+        if (whole && o.nwg <= RBFFD_STEP_TILES) o.ord = b.take<int4>(2 * o.nwg + 1);
     } else {
         o.st_curl = b.take<int32_t>(o.Nt * o.n);
         o.st_hv = o.nh > 0 ? b.take<int32_t>(o.Nt * o.nh) : nullptr;
@@ -138,8 +139,8 @@ int64_t layout_arena(rbffd_plan* p, char* base, int64_t* ws, int64_t* adj_ws) {
     layout_set(b, p->E, p->dim, true, has_wall_normals(p));
     if (!p->collocated) layout_set(b, p->H, p->dim, false, false);
     const int cb = chunk_bytes(p->p.wdtype);
-    layout_block(b, p->opH, p->dim, wb, cb, p->K, p->p.adjoint != 0);
-    if (!p->collocated) layout_block(b, p->opE, p->dim, wb, cb, p->K, false);
+    layout_block(b, p->opH, p->dim, wb, cb, p->K, p->p.adjoint != 0, can_step_whole(p));
+    if (!p->collocated) layout_block(b, p->opE, p->dim, wb, cb, p->K, false, false);
     else {
         // the E update uses the same operator block
         OpBlock keep = p->opE;

@@ -1731,6 +1731,85 @@ int build_transpose(rbffd_plan* p, void* wsp, hipStream_t st) {
     return RBFFD_OK;
 }
 
+namespace {
+// Order of the staged tiles for whole steps: strips one tile high, so that what a
+// tile's halo touches starts soon before or after it.  The key is the strip and x
+// of the tile's centroid; wide: a tile of several parts (the curve jumps).
+__global__ __launch_bounds__(64) void k_tkeys(const double* xyz, int64_t N, double lo_x, double lo_y, double inv_w, double inv_s,
+                                              uint64_t* key, int32_t* wide) {
+    const int64_t t = blockIdx.x;
+    double x = 0, y = 0, y0 = 1e300, y1 = -1e300;
+    for (int k = threadIdx.x; k < RBFFD_WGT; k += 64) {
+        const int64_t i = min(t * RBFFD_WGT + k, N - 1);
+        x += xyz[2 * i];
+        y += xyz[2 * i + 1];
+        y0 = fmin(y0, xyz[2 * i + 1]);
+        y1 = fmax(y1, xyz[2 * i + 1]);
+    }
+    for (int m = 32; m; m >>= 1) {
+        x += __shfl_xor(x, m);
+        y += __shfl_xor(y, m);
+        y0 = fmin(y0, __shfl_xor(y0, m));
+        y1 = fmax(y1, __shfl_xor(y1, m));
+    }
+    if (threadIdx.x) return;
+    const double fx = (x / RBFFD_WGT - lo_x) * inv_w, fy = (y / RBFFD_WGT - lo_y) * inv_s;
+    const uint32_t qx = (uint32_t)(fmin(fmax(fx, 0.0), 1.0) * 4294967040.0);
+    const uint32_t qy = (uint32_t)fmin(fmax(fy, 0.0), 4294967040.0);
+    key[t] = (uint64_t)qy << 32 | qx;
+    wide[t] = (y1 - y0) * inv_s > 3.5;
+}
+
+// places of the tiles by key: a wavefront counts the smaller ones (a thread per
+// tile took 1 ms of a 10^6-node set-up)
+__global__ __launch_bounds__(64) void k_trank(const uint64_t* key, int nt, int32_t* pos, int32_t* count) {
+    const int t = blockIdx.x;
+    const uint64_t k = key[t];
+    int r = 0;
+    for (int u = threadIdx.x; u < nt; u += 64) r += key[u] < k || (key[u] == k && u < t);
+    for (int m = 32; m; m >>= 1) r += __shfl_xor(r, m);
+    if (threadIdx.x) return;
+    pos[t] = r;
+    if (t == 0) *count = 0;
+}
+
+// a tile comes twice if it is wide or its halo touches a tile (not a wide one)
+// that starts more than RBFFD_STEP_AHEAD places later
+__global__ __launch_bounds__(64) void k_tsplit(const int32_t* pos, const int32_t* wide, const int32_t* hpool, const int32_t* hoff,
+                                               int32_t* split, int32_t* count) {
+    const int t = blockIdx.x;
+    bool far = wide[t] != 0;
+    for (int k = hoff[t] + (int)threadIdx.x; k < hoff[t + 1]; k += 64) {
+        const int u = hpool[k] / RBFFD_WGT;
+        far |= !wide[u] && pos[u] - pos[t] > RBFFD_STEP_AHEAD;
+    }
+    far = __any(far);
+    if (threadIdx.x) return;
+    split[t] = far;
+    if (far) atomicAdd(count, 1);
+}
+
+__global__ __launch_bounds__(64) void k_torder(const uint64_t* key, const int32_t* split, const int32_t* hoff, int nt,
+                                               const int32_t* count, int4* ord) {
+    const int t = blockIdx.x;
+    const uint64_t k = key[t];
+    const int s = split[t], S = *count;
+    int r = 0;
+    for (int u = threadIdx.x; u < nt; u += 64) r += split[u] == s && (key[u] < k || (key[u] == k && u < t));
+    for (int m = 32; m; m >>= 1) r += __shfl_xor(r, m);
+    if (threadIdx.x) return;
+    int4 job = make_int4(t, 0, hoff[t], hoff[t + 1] - hoff[t]);
+    if (s) {
+        job.y = kOnlyH;
+        ord[r] = job;
+        job.y = kOnlyE;
+        ord[nt + r] = job;
+    } else {
+        ord[S + r] = job;
+    }
+}
+}  // namespace
+
 int build_halos(rbffd_plan* p, void* wsp, hipStream_t st) {
     OpBlock& o = p->opH;
     o.hmax = 0;
@@ -1759,6 +1838,21 @@ int build_halos(rbffd_plan* p, void* wsp, hipStream_t st) {
     HIPCHK(p, hipGetLastError());
     std::vector<int32_t> off(o.nwg + 1);
     HIPCHK(p, hipMemcpyAsync(off.data(), o.hoff, (o.nwg + 1) * 4, hipMemcpyDeviceToHost, st));
+    if (o.ord) {
+        const int nt = (int)o.nwg;
+        uint64_t* key = kin;   // the sort's input is no longer needed
+        int32_t *rank = flag, *split = flag + nt, *wide = flag + 2 * nt, *count = (int32_t*)(o.ord + 2 * nt);
+        const double w = p->p.hi[0] - p->p.lo[0];
+        const double side = std::sqrt(w * (p->p.hi[1] - p->p.lo[1]) * RBFFD_WGT / (double)N);   // of a tile
+        const dim3 nb(nt);
+        hipLaunchKernelGGL(k_tkeys, nb, dim3(64), 0, st, p->E.xyz, N, p->p.lo[0], p->p.lo[1], w > 0 ? 1 / w : 0.0,
+                           side > 0 ? 1 / side : 0.0, key, wide);
+        hipLaunchKernelGGL(k_trank, nb, dim3(64), 0, st, key, nt, rank, count);
+        hipLaunchKernelGGL(k_tsplit, nb, dim3(64), 0, st, rank, wide, o.hpool, o.hoff, split, count);
+        hipLaunchKernelGGL(k_torder, nb, dim3(64), 0, st, key, split, o.hoff, nt, count, o.ord);
+        HIPCHK(p, hipGetLastError());
+        HIPCHK(p, hipMemcpyAsync(&o.split, count, 4, hipMemcpyDeviceToHost, st));
+    }
     HIPCHK(p, hipStreamSynchronize(st));
     int32_t mx = 0;
     for (int64_t t = 0; t < o.nwg; ++t) mx = std::max(mx, off[t + 1] - off[t]);
