@@ -2489,7 +2489,8 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
     int c = f->cur;
     for (int n = 0; n < a->T;) {
         const int plain = graphs ? plain_steps(a, n) : 0;
-        if (plain >= RBFFD_GRAPH_MIN_STEPS) {
+        // the steps that fill no graph go first: the GPU is at them during the capture
+        if (plain >= RBFFD_GRAPH_MIN_STEPS && plain % RBFFD_GRAPH_STEPS == 0) {
             int done = 0;
             rc = replay_steps(
                 p, plain, c, st,
