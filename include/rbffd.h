@@ -166,7 +166,8 @@ typedef struct rbffd_fields {
  *  - checkpoints: if ckpt != NULL the state (E^n, H^n) is copied to slot
  *    n / ckpt_every for every n multiple of ckpt_every, n < T; one slot is
  *    e_bytes + h_bytes long (E first).
- *  - use_graph: capture the step loop in a HIP graph and replay it.
+ *  - use_graph: let steps be replayed from a HIP graph, done where launching
+ *    is bound by the host (few tiles, many steps with nothing due between).
  *  - unstable_threshold: > 0 makes the run fail with RBFFD_EUNSTABLE if an
  *    energy sample is NaN or exceeds threshold * energy_out[0].
  * The plan's precision templates apply; src_amp, src_wave are double for F64
@@ -390,7 +391,9 @@ int rbffd_autotune_cached(rbffd_plan* plan, rbffd_fields* f, int32_t reps, const
  * width of its staged ones: 16 fields for persist >= 16 where two
  * workgroups' slices fit one CU's LDS, 4 below 8, else 8, each where K and
  * the LDS allow; batch plans start at persist = 16).  A plan starts on a variant
- * chosen by its size and precision.  rbffd_set_variant sets
+ * chosen by its size and precision.  Inside rbffd_run a 2D FP32 TMz plan on the
+ * staged kernels (lds = 1) may take each step as one kernel, with the same
+ * results.  rbffd_set_variant sets
  * it (block a multiple of 64, <= 512, lds 0..3). */
 int rbffd_get_variant(const rbffd_plan* plan, int32_t* out_variant);
 int rbffd_set_variant(rbffd_plan* plan, int32_t block, int32_t xcd, int32_t lds, int32_t persist);

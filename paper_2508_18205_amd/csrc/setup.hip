@@ -1735,8 +1735,8 @@ namespace {
 // Order of the staged tiles for whole steps: strips one tile high, so that what a
 // tile's halo touches starts soon before or after it.  The key is the strip and x
 // of the tile's centroid; wide: a tile of several parts (the curve jumps).
-__global__ __launch_bounds__(64) void k_tkeys(const double* xyz, int64_t N, double lo_x, double lo_y, double inv_w, double inv_s,
-                                              uint64_t* key, int32_t* wide) {
+__global__ __launch_bounds__(64) void k_tkeys(const double* xyz, int64_t N, double lo_x, double lo_y, double inv_w,
+                                              double inv_s, uint64_t* key, int32_t* wide) {
     const int64_t t = blockIdx.x;
     double x = 0, y = 0, y0 = 1e300, y1 = -1e300;
     for (int k = threadIdx.x; k < RBFFD_WGT; k += 64) {
@@ -1775,8 +1775,8 @@ __global__ __launch_bounds__(64) void k_trank(const uint64_t* key, int nt, int32
 
 // a tile comes twice if it is wide or its halo touches a tile (not a wide one)
 // that starts more than RBFFD_STEP_AHEAD places later
-__global__ __launch_bounds__(64) void k_tsplit(const int32_t* pos, const int32_t* wide, const int32_t* hpool, const int32_t* hoff,
-                                               int32_t* split, int32_t* count) {
+__global__ __launch_bounds__(64) void k_tsplit(const int32_t* pos, const int32_t* wide, const int32_t* hpool,
+                                               const int32_t* hoff, int32_t* split, int32_t* count) {
     const int t = blockIdx.x;
     bool far = wide[t] != 0;
     for (int k = hoff[t] + (int)threadIdx.x; k < hoff[t + 1]; k += 64) {
