@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -43,11 +44,15 @@
 #define RBFFD_BAND_HI ((int64_t)76 << 20)
 #define RBFFD_BAND_NODE 512
 #define RBFFD_CACHED_F32 120000
-// Whole steps (step.hip): most tiles (their flags lie in the run workspace), how long
-// a workgroup waits for its neighbours' H before it computes it itself (ticks of 10
-// ns; the waits seen are below 10 us), and how many places ahead in the order of
-// dispatch a tile may look: a third to a half of the workgroups a chip holds
+// Whole steps (step.hip): most tiles; how many runs of a plan have flags of their own
+// (two in flight on the same flags wait for tiles whose flags the other overwrote: two
+// streams on one 1M-node plan, us per step of both, 405 on shared flags, 191 on their
+// own, 255 in halves); how long a workgroup waits for its neighbours' H before it
+// computes it itself (ticks of 10 ns; the waits seen are below 10 us); and how many
+// places ahead in the order of dispatch a tile may look: a third to a half of the
+// workgroups a chip holds
 #define RBFFD_STEP_TILES 16384
+#define RBFFD_STEP_RUNS 64
 #define RBFFD_STEP_PATIENCE 5000
 #define RBFFD_STEP_AHEAD 256
 #define RBFFD_KSLICE 16           // widest field slice of the staged K-field batch
@@ -101,6 +106,9 @@ struct OpBlock {
     // length of the halo list), then the count of those tiles
     int4* ord = nullptr;
     int32_t split = 0;             // that count on the host
+    // whole steps: [RBFFD_STEP_RUNS][nwg] the run and step each tile's H is at; runs
+    // of the plan take the rows in turn
+    uint64_t* flags = nullptr;
     int32_t Q8 = 0;
     int64_t nwg = 0;
     int32_t wgt = RBFFD_WGT;       // nodes per staged workgroup tile (halo lists)
@@ -164,6 +172,7 @@ struct rbffd_plan {
     // private stream used only to capture HIP graphs (the caller's stream may
     // be the legacy null stream, which cannot be captured); default priority
     mutable hipStream_t cap_stream = nullptr;
+    mutable std::atomic<uint32_t> whole_runs{0};   // runs that took whole steps so far (OpBlock::flags)
     std::string err;
     // Morton quantisation box (square): lo and common side
     double mlo[3] = {0, 0, 0};
@@ -189,12 +198,10 @@ inline bool can_step_whole(const rbffd_plan* p) {
 constexpr int RED_BLOCKS = 1024;
 struct RunWS {
     double* part;       // [RED_BLOCKS * 12]
-    uint64_t* flags;    // [RBFFD_STEP_TILES] whole steps: the run and step each tile's H is at
 };
 inline RunWS run_ws(void* ws) {   // fits the smallest workspace (1 MB)
     RunWS w;
     w.part = (double*)ws;
-    w.flags = (uint64_t*)(w.part + RED_BLOCKS * 12);
     return w;
 }
 

@@ -102,7 +102,10 @@ void layout_block(Bump& b, OpBlock& o, int dim, int wb, int cb, int K, bool adjo
         if (K > 1) o.lself = b.take<uint16_t>(T);
         o.hpool = b.take<int32_t>(o.Nt * o.ns);
         o.hoff = b.take<int32_t>(o.nwg + 1);
-        if (whole && o.nwg <= RBFFD_STEP_TILES) o.ord = b.take<int4>(2 * o.nwg + 1);
+        if (whole && o.nwg <= RBFFD_STEP_TILES) {
+            o.ord = b.take<int4>(2 * o.nwg + 1);
+            o.flags = b.take<uint64_t>(RBFFD_STEP_RUNS * o.nwg);
+        }
     } else {
         o.st_curl = b.take<int32_t>(o.Nt * o.n);
         o.st_hv = o.nh > 0 ? b.take<int32_t>(o.Nt * o.nh) : nullptr;

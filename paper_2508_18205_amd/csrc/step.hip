@@ -16,7 +16,6 @@
 // indices and weights with 16-byte loads and gather field values through the
 // L2 (nodes are Morton ordered, tiles are mapped XCD-contiguously).
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -1518,7 +1517,7 @@ __global__ __launch_bounds__(256, QV <= 8 ? 3 : 2) void k_step2(A a) {
         __builtin_amdgcn_s_sleep(1);
     }
     if (__syncthreads_or(!ok)) {
-        // ascending, each once: another run on the same workspace may overwrite flags
+        // ascending, each once: a run RBFFD_STEP_RUNS later may overwrite flags
         for (int last = -1;;) {
             if (threadIdx.x == 0) want = INT32_MAX;
             __syncthreads();
@@ -2409,7 +2408,7 @@ void checkpoint(const void* E, int64_t eb, const void* H, int64_t hb, void* slot
 // part of the half-step kernels.  tag: whole steps (the run's first tag), 0: halves;
 // the sample reads only what a whole step leaves alone (E^n) or has written (H^{n+1}).
 void full_step(const rbffd_plan* p, const rbffd_fields* f, int c, int n, const rbffd_run_args* a, RunWS& w, uint64_t tag,
-               hipStream_t st) {
+               uint64_t* flags, hipStream_t st) {
     const int o = 1 - c;
     const int64_t tb = p->p.fdtype == RBFFD_F64 ? 8 : 4;   // traces, amplitudes, waveforms
     if (a->ckpt && n % a->ckpt_every == 0) {
@@ -2425,7 +2424,7 @@ void full_step(const rbffd_plan* p, const rbffd_fields* f, int c, int n, const r
     }
     const void* wave = (const char*)a->src_wave + ((int64_t)n + a->step0) * a->n_src * tb;
     fold_sources(x, a->n_src, a->src_node, a->src_amp, wave);
-    if (tag) whole_step(p, f->E[c], f->H[c], f->E[o], f->H[o], f->eps_r, x, tag + n, w.flags, st);
+    if (tag) whole_step(p, f->E[c], f->H[c], f->E[o], f->H[o], f->eps_r, x, tag + n, flags, st);
     else half(p, true, f->E[c], f->H[c], f->H[o], nullptr, st, x);
     if (a->energy_out && a->energy_every > 0 && n % a->energy_every == 0)
         energy(p, f->E[c], f->H[c], f->H[o], a->energy_out + n / a->energy_every, w, st);
@@ -2479,13 +2478,15 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
     if (a->ckpt && a->ckpt_every <= 0) return set_err(p, RBFFD_EINVAL, "ckpt_every must be positive");
     if (a->energy_out && a->energy_every < 0) return set_err(p, RBFFD_EINVAL, "energy_every < 0");
     RunWS w = run_ws(ws);
-    // tags differ between runs: two at once on one workspace take each other's flags
-    // for missing ones and compute more, not wrongly
-    static std::atomic<uint32_t> runs{0};
-    const uint64_t tag = a->T > 0 && whole_steps(p) ? (uint64_t)++runs << 32 | 1 : 0;
+    // runs in flight together (streams, replayed captures) have flags of their own; where
+    // more than RBFFD_STEP_RUNS meet, the tags differ: flags that a later run overwrote
+    // count as missing, and a workgroup computes more, not wrongly
+    const uint32_t run = a->T > 0 && whole_steps(p) ? ++p->whole_runs : 0;
+    const uint64_t tag = run ? (uint64_t)run << 32 | 1 : 0;
+    uint64_t* flags = run ? p->opH.flags + run % RBFFD_STEP_RUNS * p->opH.nwg : nullptr;
     const bool graphs = !tag && a->use_graph && a->n_src <= 0 && a->n_rcv <= 0 && p->opE.tiles <= RBFFD_GRAPH_TILES;
     if (tag)
-        hipLaunchKernelGGL(k_no_steps, dim3((unsigned)cdiv(p->opH.nwg, 256)), dim3(256), 0, st, w.flags, (int)p->opH.nwg);
+        hipLaunchKernelGGL(k_no_steps, dim3((unsigned)cdiv(p->opH.nwg, 256)), dim3(256), 0, st, flags, (int)p->opH.nwg);
     int c = f->cur;
     for (int n = 0; n < a->T;) {
         const int plain = graphs ? plain_steps(a, n) : 0;
@@ -2503,7 +2504,7 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
             n += done;   // even: the buffers are back at c
             if (done > 0) continue;
         }
-        full_step(p, f, c, n, a, w, tag, st);
+        full_step(p, f, c, n, a, w, tag, flags, st);
         c = 1 - c;
         ++n;
     }
