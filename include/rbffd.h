@@ -398,6 +398,17 @@ int rbffd_autotune_cached(rbffd_plan* plan, rbffd_fields* f, int32_t reps, const
 int rbffd_get_variant(const rbffd_plan* plan, int32_t* out_variant);
 int rbffd_set_variant(rbffd_plan* plan, int32_t block, int32_t xcd, int32_t lds, int32_t persist);
 
+/* rbffd_whole_steps: whether rbffd_run takes each step as one kernel with the
+ * present variant (out[0], 0 or 1), its workgroup tiles (out[1]), how many of
+ * them come twice (their H update first of all, their E update last; out[2]), and
+ * how many tiles' H updates were done so far by workgroups that had waited in vain
+ * for them (out[3], host int64 [4]).  A workgroup waits until the tiles around
+ * its own have been updated, at most `ticks` of 10 ns (rbffd_set_patience, >= 0),
+ * and then updates them itself, with the same results; more than a few such
+ * tiles per step say that other work on the GPU keeps workgroups from starting. */
+int rbffd_whole_steps(const rbffd_plan* plan, int64_t* out_host, void* stream);
+int rbffd_set_patience(rbffd_plan* plan, int32_t ticks);
+
 /* ---- measurement ------------------------------------------------------------
  * rbffd_stream_copy: dst[0 .. bytes) = src[0 .. bytes) on the stream with 16-byte
  * non-temporal accesses (device pointers, 16-byte aligned, bytes a multiple of

@@ -103,7 +103,8 @@ struct OpBlock {
     // whole steps (2D, single field): what each workgroup does, in order of dispatch.
     // Tiles whose halo reaches far in that order come twice: their H update first of
     // all, their E update last.  [2 nwg] (tile, kOnlyH or kOnlyE or 0, start and
-    // length of the halo list), then the count of those tiles
+    // length of the halo list), then the count of those tiles and the count of H
+    // tiles that waiting workgroups computed by themselves so far
     int4* ord = nullptr;
     int32_t split = 0;             // that count on the host
     // whole steps: [RBFFD_STEP_RUNS][nwg] the run and step each tile's H is at; runs
@@ -169,6 +170,7 @@ struct rbffd_plan {
     char* arena = nullptr;
     bool ready = false;
     Variant var;
+    int32_t patience = RBFFD_STEP_PATIENCE;   // whole steps
     // private stream used only to capture HIP graphs (the caller's stream may
     // be the legacy null stream, which cannot be captured); default priority
     mutable hipStream_t cap_stream = nullptr;

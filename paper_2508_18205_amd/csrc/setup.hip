@@ -1770,7 +1770,7 @@ __global__ __launch_bounds__(64) void k_trank(const uint64_t* key, int nt, int32
     for (int m = 32; m; m >>= 1) r += __shfl_xor(r, m);
     if (threadIdx.x) return;
     pos[t] = r;
-    if (t == 0) *count = 0;
+    if (t == 0) count[0] = count[1] = 0;
 }
 
 // a tile comes twice if it is wide or its halo touches a tile (not a wide one)

@@ -1342,7 +1342,7 @@ __global__ __launch_bounds__(256) void k_e2l(A a) {
 // lane) from the H update to the E update.  Between the two it publishes the tile's
 // H and waits for the tiles that its halo touches.  Tiles are dispatched in strips
 // (OpBlock::ord), so these run at about the same time; a workgroup that has waited
-// RBFFD_STEP_PATIENCE computes the missing H by itself from E^n and H^n, which
+// its patience out computes the missing H by itself from E^n and H^n, which
 // nobody writes meanwhile, to the same bits: it never depends on another's progress.
 // The sums are those of the staged kernels, in their order.
 // us per step, two halves / whole, 2D FP32: 40k nodes (n 25) 17.0 / 11.2, 90k 18.8 /
@@ -1359,7 +1359,9 @@ struct Whole : B {   // a: the factor of the E update, out: E^{n+1}
     uint64_t* flags;      // [nwg] tag of the tile's latest H
     uint64_t tag;         // this run and step
     const int4* ord;      // what each workgroup does (OpBlock)
+    int32_t* late;        // H tiles computed by workgroups that had waited (OpBlock)
     double aH;
+    int32_t patience;     // ticks of 10 ns
 };
 
 __device__ __forceinline__ uint64_t pair_bits(float x, float y) {
@@ -1505,7 +1507,7 @@ __global__ __launch_bounds__(256, QV <= 8 ? 3 : 2) void k_step2(A a) {
         if (in) record_receivers<float, float>(a, i);
         if (job & kOnlyH) return;
     }
-    // H of the halo's tiles, within RBFFD_STEP_PATIENCE; then what is missing is
+    // H of the halo's tiles, as long as the patience lasts; then what is missing is
     // computed here as well, so that no order of dispatch can keep a workgroup waiting
     const uint64_t t0 = wall_clock64();
     bool ok;
@@ -1513,7 +1515,7 @@ __global__ __launch_bounds__(256, QV <= 8 ? 3 : 2) void k_step2(A a) {
         ok = true;
         for (int k = (int)threadIdx.x; k < hc; k += 256)
             ok &= __hip_atomic_load(a.flags + list[k] / RBFFD_WGT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.tag;
-        if (__all(ok) || wall_clock64() - t0 > RBFFD_STEP_PATIENCE) break;
+        if (__all(ok) || wall_clock64() - t0 > (uint64_t)a.patience) break;
         __builtin_amdgcn_s_sleep(1);
     }
     if (__syncthreads_or(!ok)) {
@@ -1535,6 +1537,7 @@ __global__ __launch_bounds__(256, QV <= 8 ? 3 : 2) void k_step2(A a) {
             __syncthreads();
             if (threadIdx.x == 0) {
                 __hip_atomic_store(a.flags + t, a.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                atomicAdd(a.late, 1);
                 stores_done();
             }
             __syncthreads();
@@ -2221,6 +2224,8 @@ void half(const rbffd_plan* p, bool hupd, const void* E, const void* H, void* ou
 using WA = SA<float, float>;
 using WX = SX<float, float>;
 
+int32_t* late_count(const OpBlock& o) { return (int32_t*)(o.ord + 2 * o.nwg) + 1; }
+
 size_t whole_lds(const OpBlock& o) { return (size_t)(((o.hmax + 3) & ~3) + 2 * o.hmax) * sizeof(float); }
 
 bool narrow(const OpBlock& o) { return o.C4 <= 6 && o.V4 <= 8; }   // three workgroups per CU, else two
@@ -2277,6 +2282,8 @@ void whole_step(const rbffd_plan* p, const void* E, const void* H, void* Eout, v
         w.flags = flags;
         w.tag = tag;
         w.ord = o.ord;
+        w.late = late_count(o);
+        w.patience = p->patience;
         w.aH = p->dt / p->p.mu0;
         launch_whole(p, w, st);
     };
@@ -2520,6 +2527,30 @@ extern "C" int rbffd_run(const rbffd_plan* p, rbffd_fields* f, const rbffd_run_a
                 return set_err(p, RBFFD_EUNSTABLE, "energy sample " + std::to_string(k) + " = " + std::to_string(e[k]) +
                                                        " exceeds the threshold");
     }
+    return RBFFD_OK;
+}
+
+extern "C" int rbffd_whole_steps(const rbffd_plan* p, int64_t* out, void* stream) {
+    if (!p || !out) return RBFFD_EINVAL;
+    if (!p->ready) return set_err(p, RBFFD_ESTATE, "rbffd_weights has not run");
+    const OpBlock& o = p->opH;
+    int32_t late = 0;
+    if (o.ord && o.hmax) {
+        hipStream_t st = (hipStream_t)stream;
+        HIPCHK(p, hipMemcpyAsync(&late, late_count(o), 4, hipMemcpyDeviceToHost, st));
+        HIPCHK(p, hipStreamSynchronize(st));
+    }
+    out[0] = whole_steps(p);
+    out[1] = o.nwg;
+    out[2] = o.split;
+    out[3] = late;
+    return RBFFD_OK;
+}
+
+extern "C" int rbffd_set_patience(rbffd_plan* p, int32_t ticks) {
+    if (!p) return RBFFD_EINVAL;
+    if (ticks < 0) return set_err(p, RBFFD_EINVAL, "patience < 0");
+    p->patience = ticks;
     return RBFFD_OK;
 }
 

@@ -408,3 +408,12 @@ class Solver:
         self.lib.rbffd_get_variant(self.plan, C.byref(v))
         return {"block": v.value & 0xFFFF, "xcd": (v.value >> 16) & 1, "lds": (v.value >> 17) & 7,
                 "persist": (v.value >> 20) & 0xFF}
+
+    def whole_steps(self):
+        """Whether runs take each step as one kernel, and how that goes (rbffd_whole_steps)."""
+        out = (C.c_int64 * 4)()
+        check(self.lib.rbffd_whole_steps(self.plan, out, self.stream()), self.plan, "rbffd_whole_steps")
+        return {"whole": bool(out[0]), "tiles": out[1], "twice": out[2], "late": out[3]}
+
+    def set_patience(self, ticks):
+        check(self.lib.rbffd_set_patience(self.plan, int(ticks)), self.plan, "set_patience")
