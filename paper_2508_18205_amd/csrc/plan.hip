@@ -164,6 +164,37 @@ int64_t layout_arena(rbffd_plan* p, char* base, int64_t* ws, int64_t* adj_ws) {
 // ---------------------------------------------------------------------------
 // Plan creation
 // ---------------------------------------------------------------------------
+namespace {
+void start_variant(rbffd_plan* p, int64_t N) {
+    // K-field batches start on the staged kernels with 16-field slices where
+    // K and the LDS allow (the tuner's usual choice), else 8 or 4
+    if (p->K > 1) {
+        p->var.persist = 16;
+        return;
+    }
+    if (p->p.fdtype == RBFFD_F64) {
+        // us per step, staged / several wavefronts per 64-node tile: 2D n = 12, 40k
+        // nodes 17.3 / 10.7, 62k 18.4 / 14.2, 90k 21.2 / 20.1, 250k 47 / 51; 3D 13.5k
+        // 44.6 / 15.0, 30k 46.5 / 27.1, 64k 51.2 / 48.9, 125k 73 / 91
+        p->var.lds = N <= (p->dim == 2 ? RBFFD_SMALL_2D : RBFFD_SMALL) ? 3 : 1;
+        return;
+    }
+    // FP32 and BF16: small sets start on kernels with the staged ones' order of
+    // summation: in 3D the tile kernel (us per step, staged / it: 13.5k nodes 46.3 /
+    // 14.5, 30k 47.0 / 30.8), then global gathers (30k 47.0 / 29.7, 64k 48.9 / 32.9,
+    // 91k 50.7 / 52.3); in 2D global gathers (n = 12, 40k nodes 16.2 / 11.6, 90k 17.8 /
+    // 16.4, 109k 18.4 / 19.2; n = 60, 62k 27.2 / 24.4, 90k 29.7 / 32.1).  One tile per
+    // workgroup while there are fewer than a few per CU (2D n = 60, four / one, staged:
+    // 1.6k nodes 17.3 / 14.2, 14.3; 32k 18.1 / 15.0, 25.6; 53k 24.0 / 23.6; 3D n = 35, 27k
+    // 27.8 / 22.9, 64k 33.3 / 33.7).
+    if (p->dim == 3 && N <= RBFFD_SMALL_3D_F32) p->var.lds = 3;
+    else if (N <= RBFFD_SMALL) {
+        p->var.lds = 0;
+        if (p->collocated && N <= RBFFD_SMALL_BLOCK) p->var.block = RBFFD_TILE;
+    }
+}
+}  // namespace
+
 extern "C" int rbffd_plan_create(const rbffd_params* prm, int64_t N, const double* xyz_host,
                                  const uint8_t* flags_host, int64_t N_h, const double* xyzH_host,
                                  const uint8_t* flagsH_host, rbffd_plan** out) {
@@ -218,21 +249,6 @@ extern "C" int rbffd_plan_create(const rbffd_params* prm, int64_t N, const doubl
     p->dim = q.dim;
     p->collocated = q.mode != RBFFD_MODE_STAG2;
     p->K = q.K;
-    // K-field batches start on the staged kernels with 16-field slices where
-    // K and the LDS allow (the tuner's usual choice), else 8 or 4
-    if (q.K > 1) p->var.persist = 16;
-    // Small node sets: the staged kernels have too few workgroups to fill the
-    // chip.  FP64 plans start on the kernels with several wavefronts per 64-node
-    // tile (us per step, staged / small: 2D n = 12, 40k nodes 17.3 / 10.7, 62k
-    // 18.4 / 14.2, 90k 21.2 / 20.1, 250k 47 / 51; 3D 13.5k 44.6 / 15.0, 30k 46.5 /
-    // 27.1, 64k 51.2 / 48.9, 125k 73 / 91).  FP32 plans start on kernels with the
-    // staged ones' order of summation: in 3D the tile kernel (13.5k nodes 46.3 /
-    // 14.5, 30k 47.0 / 30.8), then global gathers (30k 47.0 / 29.7, 64k 48.9 /
-    // 32.9, 91k 50.7 / 52.3); in 2D global gathers (n = 12, 40k nodes 16.2 / 11.6,
-    // 90k 17.8 / 16.4, 109k 18.4 / 19.2; n = 60, 62k 27.2 / 24.4, 90k 29.7 / 32.1).
-    else if (q.fdtype == RBFFD_F64) p->var.lds = N <= (q.dim == 2 ? RBFFD_SMALL_2D : RBFFD_SMALL) ? 3 : 1;
-    else if (q.dim == 3 && N <= RBFFD_SMALL_3D_F32) p->var.lds = 3;
-    else if (N <= RBFFD_SMALL) p->var.lds = 0;
     p->n = q.n;
     p->M = (int)n_monomials(q.dim, q.m);
     if (p->M > RBFFD_MAX_MONO) return fail(RBFFD_ESIZE, "too many monomials for the curl system");
@@ -247,6 +263,7 @@ extern "C" int rbffd_plan_create(const rbffd_params* prm, int64_t N, const doubl
     }
     p->ns = std::max(p->n, p->nh);
     if (p->ns > RBFFD_MAX_STENCIL) return fail(RBFFD_ESIZE, "stencil larger than 128");
+    start_variant(p, N);
     fill_exponents(q.dim, q.m, p->ex_m);
     if (q.hv_alpha > 0) fill_exponents(q.dim, 2 * q.hv_alpha, p->ex_h);
 
