@@ -23,9 +23,13 @@
                                    // workgroup per CU; the tuner also tries one operand
                                    // at a time, two per CU)
 #define RBFFD_SMALL 65536         // node counts up to which single-field plans do not
-#define RBFFD_SMALL_2D 80000      // start on the staged kernels (plan.hip)
-#define RBFFD_SMALL_3D_F32 24576
-#define RBFFD_SMALL_BLOCK 40000   // and, in FP32, on one tile per workgroup
+#define RBFFD_SMALL_3D_F32 24576  // start on the staged kernels (plan.hip): FP32, BF16
+#define RBFFD_SMALL_BLOCK 40000   // of these, one tile per workgroup
+#define RBFFD_SMALL_2D 80000      // FP64, with at most this many weights
+#define RBFFD_SMALL_3D 50000
+#define RBFFD_SMALL_WEIGHTS 7000000
+#define RBFFD_SMALL_2D_ANY 42000  // FP64, with any stencils
+#define RBFFD_SMALL_3D_ANY 28000
 // Operators (weights, positions) up to this size stay in the 256 MB memory-side
 // cache between half steps, below 32 MB in the L2s, when loaded ordinarily; larger
 // ones stream through it.  us per step, non-temporal / ordinary loads: 2D FP32 68k

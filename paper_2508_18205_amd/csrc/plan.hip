@@ -165,6 +165,22 @@ int64_t layout_arena(rbffd_plan* p, char* base, int64_t* ws, int64_t* adj_ws) {
 // Plan creation
 // ---------------------------------------------------------------------------
 namespace {
+// Whether an FP64 plan of N nodes starts on the kernels with several wavefronts per
+// 64-node tile.  The staged kernels have too few workgroups to fill the chip with a
+// small set, but read each value once, which decides where there is much to read.
+// us per step, staged / small: 2D n 12, 40k nodes 12.5 / 11.1, 80k 19.6 / 18.5, 250k
+// 47 / 51; n 25 80k 24.0 / 22.4; n 25 alpha 3 62k 24.7 / 24.1, 70k 27.5 / 28.6; n 60
+// 40k 23.1 / 21.8, 53k 26.3 / 28.4; n 100 40k 32.1 / 31.2, 53k 36.3 / 41.8; 3D n 20
+// (alpha 1) 47k 20.2 / 19.3, 55k 21.4 / 23.6; n 35 14k 34.7 / 14.9, 36k 37.8 / 36.5,
+// 47k 37.4 / 38.4, 64k 42.0 / 49.2; n 60 27k 41.1 / 34.9, 36k 42.3 / 46.5; n 110 27k
+// 56.0 / 51.4.  Two node sets have no staged kernels: 62k nodes (n 12) 17.6 / 12.9.
+bool starts_small_f64(const rbffd_plan* p, int64_t N) {
+    if (!p->collocated) return N <= RBFFD_SMALL_2D;
+    const int64_t weights = N * (p->dim * (p->n - 1) + std::max(p->nh - 1, 0));
+    if (p->dim == 2) return N <= RBFFD_SMALL_2D_ANY || (N <= RBFFD_SMALL_2D && weights <= RBFFD_SMALL_WEIGHTS);
+    return N <= RBFFD_SMALL_3D_ANY || (N <= RBFFD_SMALL_3D && weights <= RBFFD_SMALL_WEIGHTS);
+}
+
 void start_variant(rbffd_plan* p, int64_t N) {
     // K-field batches start on the staged kernels with 16-field slices where
     // K and the LDS allow (the tuner's usual choice), else 8 or 4
@@ -173,10 +189,7 @@ void start_variant(rbffd_plan* p, int64_t N) {
         return;
     }
     if (p->p.fdtype == RBFFD_F64) {
-        // us per step, staged / several wavefronts per 64-node tile: 2D n = 12, 40k
-        // nodes 17.3 / 10.7, 62k 18.4 / 14.2, 90k 21.2 / 20.1, 250k 47 / 51; 3D 13.5k
-        // 44.6 / 15.0, 30k 46.5 / 27.1, 64k 51.2 / 48.9, 125k 73 / 91
-        p->var.lds = N <= (p->dim == 2 ? RBFFD_SMALL_2D : RBFFD_SMALL) ? 3 : 1;
+        p->var.lds = starts_small_f64(p, N) ? 3 : 1;
         return;
     }
     // FP32 and BF16: small sets start on kernels with the staged ones' order of

@@ -11,7 +11,7 @@ import pytest
 from test_abi import _params
 
 GLOBAL, STAGED, SMALL = 0, 1, 3
-F32, BF16 = dict(wdtype=1, fdtype=1), dict(wdtype=1, fdtype=2)
+F64, F32, BF16 = dict(wdtype=0, fdtype=0), dict(wdtype=1, fdtype=1), dict(wdtype=1, fdtype=2)
 
 
 def _variant(N, dim=2, **kw):
@@ -40,3 +40,14 @@ def _variant(N, dim=2, **kw):
     (24577, dict(F32, dim=3, n=35), GLOBAL, 64), (65537, dict(F32, dim=3, n=35), STAGED, 256)])
 def test_fp32(N, kw, lds, block):
     assert _variant(N, **kw) == (lds, block)
+
+
+@pytest.mark.parametrize("N,kw,lds", [
+    (80000, dict(n=25), SMALL), (80001, dict(n=25), STAGED), (80000, dict(n=25, mode=2), SMALL),
+    (62500, dict(n=25, m=4, hv_alpha=3), SMALL), (70225, dict(n=25, m=4, hv_alpha=3), STAGED),
+    (42000, dict(n=120), SMALL), (52900, dict(n=60), STAGED),
+    (46656, dict(dim=3, n=20, hv_alpha=1), SMALL), (54872, dict(dim=3, n=20, hv_alpha=1), STAGED),
+    (35937, dict(dim=3, n=35), SMALL), (46656, dict(dim=3, n=35), STAGED),
+    (27000, dict(dim=3, n=110), SMALL), (35937, dict(dim=3, n=60), STAGED)])
+def test_fp64(N, kw, lds):
+    assert _variant(N, **F64, **kw) == (lds, 256)
