@@ -216,6 +216,8 @@ class Solver:
         H = [torch.zeros((n, self.FH), dtype=self.dtype, device=self.device) for _ in range(2)]
         er = None
         if eps_r is not None:
+            if tuple(eps_r.shape) != (self.N,):
+                raise ValueError(f"eps_r has shape {tuple(eps_r.shape)}, the node set {self.N} nodes")
             er = self.permute(eps_r.detach().to(device=self.device, dtype=self.cdtype).reshape(-1, 1).contiguous()).reshape(-1)
         return State(E, H, 0, er)
 
