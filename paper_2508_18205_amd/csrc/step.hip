@@ -1368,7 +1368,15 @@ __device__ __forceinline__ uint64_t pair_bits(float x, float y) {
     return (uint64_t)__float_as_uint(y) << 32 | __float_as_uint(x);
 }
 
-// Stores of this wavefront have reached the point that all XCDs see
+// Stores of this wavefront have reached the point that all XCDs see.  H and the flags
+// are handed over by relaxed agent-scope atomics alone (an agent-scope release or
+// acquire would write back or invalidate the XCD's L2, where the operator lies), which
+// rests on the following of gfx950: such loads and stores carry sc1 and pass the L2s in
+// both directions, stores count in vmcnt until that point has them, and a load issued
+// after the flag's value was used (a barrier lies between them) reads later.
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "k_step2 hands H over between workgroups in a way that is shown for gfx950 only"
+#endif
 __device__ __forceinline__ void stores_done() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
