@@ -22,8 +22,6 @@ SOURCES = ["plan.hip", "setup.hip", "step.hip", "batched.hip", "adjoint.hip", "p
 FLAGS = [
     "-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the register-resident solver's elimination is unrolled over its column blocks
-    "-mllvm", "-pragma-unroll-threshold=262144",
     "-I", os.path.join(ROOT, "include"), "-Wno-unused-result",
 ]
 
