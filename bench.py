@@ -9,8 +9,9 @@ over all nodes; inputs are resident in HBM before timing starts.
 Prints ONE JSON line.  Besides the headline FP32 node-steps/s it reports the
 FP64 rate on the same nodes, the FP32-vs-FP64 relative L2 difference after the
 workload's 10^4 steps, the K = 64 batched rate (250k-node jittered grid), the
-roofline of the dominant kernel (the H update) and the FP64 CPU oracle timed on
-a bounded sample of the same workload.
+roofline of the kernel that a timed step launches (the whole step, or the longer
+of its two halves where it takes two) and the FP64 CPU oracle timed on a bounded
+sample of the same workload.
 """
 import argparse
 import ctypes
@@ -44,6 +45,12 @@ def alg_bytes_half(n, nh, d, sw, sf, fe, fh, which):
     return ns * 4 + (d * n + nh) * sw + fields * sf
 
 
+def alg_bytes_step(n, nh, d, sw, sf, fe, fh):
+    """The same for a whole step in one kernel: the indices and weights once,
+    every field value read once and written once."""
+    return max(n, nh) * 4 + (d * n + nh) * sw + 2 * (fe + fh) * sf
+
+
 def time_halves(s, st, reps, torch):
     """Average duration of each half-update kernel: reps back-to-back launches
     between one HIP event pair on the library's stream.  The field structs are
@@ -73,6 +80,19 @@ def time_halves(s, st, reps, torch):
     return out
 
 
+def time_run(s, st, reps, torch):
+    """Average duration of one step of a run of ``reps`` steps."""
+    stream = torch.cuda.current_stream()
+    s.run(st, 2)
+    e0 = torch.cuda.Event(enable_timing=True)
+    e1 = torch.cuda.Event(enable_timing=True)
+    e0.record(stream)
+    s.run(st, reps)
+    e1.record(stream)
+    e1.synchronize()
+    return e0.elapsed_time(e1) / reps * 1e-3
+
+
 def dispersion_l1(samples, every, jmax=45):
     """||err||_1 of the propagation speed (Section 6, eq. 24-26) from line
     samples [N_t, N_x]: Hann window in time, transform pairing e^{-ikx} with
@@ -90,7 +110,7 @@ def dispersion_l1(samples, every, jmax=45):
 
 
 def counted_traffic(kernel):
-    """HBM bytes per launch of ``kernel`` (e.g. "k_h2l<float,float>") from the
+    """HBM bytes per launch of ``kernel`` (e.g. "k_step2<8,16>") from the
     committed counter summary: FETCH_SIZE and WRITE_SIZE, each scaled by what
     the same counter reads for the 2 GiB copy probe (the per-size request
     counts give the same bytes to 0.01 %).  None unless the step-kernel
@@ -214,8 +234,9 @@ def vs_oracle(s, st, energy, g, whole_vector=False):
 def kernels_only(args):
     """Average duration of each half-update kernel of the named plans, with
     the same autotuned variant the benchmark uses, from rbffd_half launches
-    alone (no graph replay): the process runs only the set-up, the tuner and
-    these launches, for per-kernel profiler counters."""
+    alone (no graph replay), and of the whole step where a run takes those: the
+    process runs only the set-up, the tuner and these launches, for per-kernel
+    profiler counters."""
     import numpy as np
     import torch
     from synth import configs
@@ -280,6 +301,8 @@ def kernels_only(args):
         th, te = time_halves(s, st, args.kernel_reps, torch)
         out[name] = {"N": w.N, "h_update_us": round(th * 1e6, 2), "e_update_us": round(te * 1e6, 2),
                      "variant": s.variant()}
+        if s.whole_steps()["whole"]:
+            out[name]["step_us"] = round(time_run(s, st, args.kernel_reps, torch) * 1e6, 2)
         log(f"{name}: {out[name]}")
         del s, st
         torch.cuda.empty_cache()
@@ -387,36 +410,44 @@ def main():
         reps.append(w.N * args.steps / (e0.elapsed_time(e1) * 1e-3))
     repeat_median = float(np.median(reps))
 
-    # roofline of the dominant kernel (H update) from HIP events on the same stream
+    # roofline of what a timed step launches, from HIP events on the same stream: the
+    # whole step where runs take those, else the longer of its two halves
     th, te = time_halves(s, st, args.kernel_reps, torch)
     sw = 8 if args.precision == "f64" else 4
     sf = {"f64": 8, "f32": 4, "bf16": 2}[args.precision]
-    bh = alg_bytes_half(w.n, w.n_hv, w.dim, sw, sf, 1, 2, 0) * w.N
-    be = alg_bytes_half(w.n, w.n_hv, w.dim, sw, sf, 1, 2, 1) * w.N
-    gbs_h = bh / th / 1e9
-    gbs_e = be / te / 1e9
-    log(f"H update {th * 1e6:.1f} us -> {gbs_h:.0f} GB/s ; E update {te * 1e6:.1f} us -> {gbs_e:.0f} GB/s")
-    dominant = "H" if th >= te else "E"
-    ach = gbs_h if dominant == "H" else gbs_e
-    staged = bool(s.variant()["lds"]) and s.sizes.N == w.N
-    kname = ("k_h2l" if dominant == "H" else "k_e2l") if staged else ("k_h2" if dominant == "H" else "k_e2")
-    traffic = None
-    if staged and args.precision == "f32" and args.scale == 1.0:
-        traffic = counted_traffic(kname + "<float,float>")
-    roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": traffic,
+    types = {"f64": "double,double", "f32": "float,float", "bf16": "bf16,float"}[args.precision]
+    v = s.variant()["lds"]
+    tail = "s" if v == 3 else ("l" if v and s.sizes.N == w.N else "")
+    halves = []
+    for which, t, name in ((0, th, "k_h2"), (1, te, "k_e2")):
+        b = alg_bytes_half(w.n, w.n_hv, w.dim, sw, sf, 1, 2, which) * w.N
+        halves.append({"kernel": f"{name}{tail}<{types}>", "achieved": round(b / t / 1e9, 1),
+                       "alg_bytes_per_launch": int(b), "avg_launch_us": round(t * 1e6, 2)})
+        log(f"{halves[-1]}")
+    whole = s.whole_steps()["whole"]
+    if whole:
+        ts = time_run(s, st, args.kernel_reps, torch)
+        b = alg_bytes_step(w.n, w.n_hv, w.dim, sw, sf, 1, 2) * w.N
+        c4, v4 = -(-(w.n - 1) // 4), -(-(w.n_hv - 1) // 4)
+        main_ = {"kernel": "k_step2<6,8>" if c4 <= 6 and v4 <= 8 else "k_step2<8,16>", "achieved": round(b / ts / 1e9, 1),
+                 "alg_bytes_per_launch": int(b), "avg_launch_us": round(ts * 1e6, 2)}
+    else:
+        main_ = dict(halves[0] if th >= te else halves[1])
+    roof = {"bound": "hbm", "achieved": main_["achieved"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(main_["achieved"] / HBM_PEAK_GBS, 4), "traffic": None,
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE and WRITE_SIZE, each scaled by the same counter read for the 2 GiB stream copy; profiles/traffic_pulse2d_1M.md)",
-            "kernel": f"{kname}<float,float> ({'H' if dominant == 'H' else 'E'} update)",
-            "alg_bytes_per_launch": int(bh if dominant == "H" else be),
-            "avg_launch_us": round((th if dominant == "H" else te) * 1e6, 2),
-            "other_half": {"achieved": round(gbs_e if dominant == "H" else gbs_h, 1),
-                           "avg_launch_us": round((te if dominant == "H" else th) * 1e6, 2)}}
-    if traffic:
-        # the staged kernels read 16-bit halo positions instead of the int32
-        # indices the algorithmic count assumes: the counted rate is lower
-        cgbs = traffic / (th if dominant == "H" else te) / 1e9
-        roof["counted_GBs"] = round(cgbs, 1)
-        roof["counted_frac"] = round(cgbs / HBM_PEAK_GBS, 4)
+            "kernel": main_["kernel"] + (" (whole step)" if whole else " (H update)" if th >= te else " (E update)"),
+            "alg_bytes_per_launch": main_["alg_bytes_per_launch"], "avg_launch_us": main_["avg_launch_us"],
+            "halves": halves}
+    if args.precision == "f32" and args.scale == 1.0:
+        for d in [roof] + halves:
+            # staged kernels read 16-bit halo positions instead of the int32
+            # indices the algorithmic count assumes: the counted rate is lower
+            traffic = counted_traffic(d["kernel"].split(" ")[0])
+            if traffic:
+                d["traffic"] = traffic
+                d["counted_GBs"] = round(traffic / d["avg_launch_us"] * 1e-3, 1)
+                d["counted_frac"] = round(d["counted_GBs"] / HBM_PEAK_GBS, 4)
     # measured streaming ceiling: the library's 16-byte copy kernel over 2 GiB
     # (read + write bytes / time)
     from paper_2508_18205_amd import _abi as _ab
