@@ -2256,6 +2256,7 @@ bool whole_steps(const rbffd_plan* p) {
         return false;
     }
     const int64_t room = (int64_t)per * cus;
+    if (room <= 0) return false;
     return o.nwg + o.split <= room || (o.nwg >= room * 7 / 4 && o.split <= o.nwg / 4);
 }
 
