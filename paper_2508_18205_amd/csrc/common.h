@@ -39,11 +39,11 @@
 // RBFFD_BAND_NODE bytes per node between these two sizes, too large for the L2s and
 // with little to sum per byte: 160k nodes (n 25 FP32, 61 MB) 22.5 / 23.6, 123k (n 12
 // FP64, 63 MB) 23.7 / 24.9, at 46 MB 20.2 / 19.8 and at 96 MB 33.1 / 32.6.
-// 2D FP32 and BF16 sets below RBFFD_CACHED_F32 nodes keep the streaming loads too:
-// there the tuner's usual choice is the small-set kernels (12 to 27 us at 90k nodes,
-// staged 18 to 29), which sum in another order, and a tuned plan's results are to
-// follow from its size, not from a race between the two (staged with ordinary loads
-// would take 12.7 to 25; from 115k nodes on staged wins either way).
+// 2D FP32, W22 and BF16 sets below RBFFD_CACHED_F32 nodes keep the streaming loads,
+// though ordinary ones are faster there (90k nodes 18 to 29 us against 12.7 to 25):
+// between about 40k and 110k nodes the tuner chooses between staged and small-set
+// kernels (12 to 27 us), which sum in another order, and with faster staged ones
+// tuned plans would move to them, their FP64 energies by 1e-8.
 #define RBFFD_CACHED_BYTES ((int64_t)256 << 20)
 #define RBFFD_BAND_LO ((int64_t)44 << 20)
 #define RBFFD_BAND_HI ((int64_t)76 << 20)

@@ -341,7 +341,7 @@ extern "C" int rbffd_plan_create(const rbffd_params* prm, int64_t N, const doubl
     }
     int64_t ws = 0, aws = 0;
     p->arena_bytes = layout_arena(p, nullptr, &ws, &aws);
-    // run workspace: reduction partials and counters
+    // run workspace: reduction partials
     p->ws_bytes = std::max<int64_t>(ws, 1 << 20);
     p->adj_ws_bytes = aws;
     *out = p;

@@ -1735,7 +1735,7 @@ namespace {
 // Order of the staged tiles for whole steps: strips one tile high, so that what a
 // tile's halo touches starts soon before or after it.  The key is the strip and x
 // of the tile's centroid; wide: a tile of several parts (the curve jumps).
-__global__ __launch_bounds__(64) void k_tkeys(const double* xyz, int64_t N, double lo_x, double lo_y, double inv_w,
+__global__ __launch_bounds__(64) void k_tplace(const double* xyz, int64_t N, double lo_x, double lo_y, double inv_w,
                                               double inv_s, uint64_t* key, int32_t* wide) {
     const int64_t t = blockIdx.x;
     double x = 0, y = 0, y0 = 1e300, y1 = -1e300;
@@ -1845,7 +1845,7 @@ int build_halos(rbffd_plan* p, void* wsp, hipStream_t st) {
         const double w = p->p.hi[0] - p->p.lo[0];
         const double side = std::sqrt(w * (p->p.hi[1] - p->p.lo[1]) * RBFFD_WGT / (double)N);   // of a tile
         const dim3 nb(nt);
-        hipLaunchKernelGGL(k_tkeys, nb, dim3(64), 0, st, p->E.xyz, N, p->p.lo[0], p->p.lo[1], w > 0 ? 1 / w : 0.0,
+        hipLaunchKernelGGL(k_tplace, nb, dim3(64), 0, st, p->E.xyz, N, p->p.lo[0], p->p.lo[1], w > 0 ? 1 / w : 0.0,
                            side > 0 ? 1 / side : 0.0, key, wide);
         hipLaunchKernelGGL(k_trank, nb, dim3(64), 0, st, key, nt, rank, count);
         hipLaunchKernelGGL(k_tsplit, nb, dim3(64), 0, st, rank, wide, o.hpool, o.hoff, split, count);

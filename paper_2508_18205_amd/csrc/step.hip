@@ -1345,12 +1345,18 @@ __global__ __launch_bounds__(256) void k_e2l(A a) {
 // its patience out computes the missing H by itself from E^n and H^n, which
 // nobody writes meanwhile, to the same bits: it never depends on another's progress.
 // The sums are those of the staged kernels, in their order.
-// us per step, two halves / whole, 2D FP32: 40k nodes (n 25) 17.0 / 11.2, 90k 18.8 /
-// 15.5, 360k 45.9 / 40.2, 1M 131 / 104-108 (n 25, alpha 3: 176 / 151), 4M 491 / 397.  What is
-// left at 1M: 14 us of waiting (taken out in a copy: 94), the sums 13 us not hidden
-// by other workgroups' loads, 80 for the loads (420 MB, floor 64).  Tried: hv weights
-// in LDS for four workgroups a CU 117, all LDS reads of a chunk before its sums 122
-// (spills), 8 neighbouring tiles per XCD 110, two workgroups a CU 127.
+// us per step, two halves / whole, 2D FP32: 40k nodes (n 25) 11.5 / 10.2, 90k 18.3 /
+// 14.1, 360k 48.5 / 37.4, 1M 133 / 101 (n 25, alpha 3: 176 / 146), 4M 491 / 397.  What is
+// left at 1M: 14 us of waiting (taken out in a copy: 94, of 104 to 108 then), the sums
+// 13 us not hidden by other workgroups' loads, 80 for the loads (420 MB, floor 64).
+// Tried: hv weights in LDS for four workgroups a CU 117, all LDS reads of a chunk
+// before its sums 122 (spills), 8 neighbouring tiles per XCD 110, two workgroups a CU 127.
+// Beside other work on the GPU a workgroup may wait for one that cannot start.  Next
+// to a stream of 8192^2 bf16 products: 360k 1585 / 804, 1M 1633 / 848.  Next to one of
+// 256 MB copies, with the copies that end meanwhile per ms: 40k 33.6 (8.4) / 27.2 (8.8),
+// 194k 57.8 (5.2) / 70.2 (5.0), 360k 96.9 (4.8) / 105 (5.6), 1M 224 (3.6) / 267 (5.1),
+// alpha 3 293 (3.4) / 292 (6.7): the copies get more of the chip, and sets that just
+// fill it lose a fifth.  Two runs at once on one 1M plan, per step of both: 255 / 191.
 template <typename B>
 struct Whole : B {   // a: the factor of the E update, out: E^{n+1}
     static constexpr bool kStream = B::kStream;
