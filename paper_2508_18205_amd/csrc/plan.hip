@@ -102,10 +102,7 @@ void layout_block(Bump& b, OpBlock& o, int dim, int wb, int cb, int K, bool adjo
         if (K > 1) o.lself = b.take<uint16_t>(T);
         o.hpool = b.take<int32_t>(o.Nt * o.ns);
         o.hoff = b.take<int32_t>(o.nwg + 1);
-        if (whole && o.nwg <= RBFFD_STEP_TILES) {
-            o.ord = b.take<int4>(2 * o.nwg + 1);
-            o.flags = b.take<uint64_t>(RBFFD_STEP_RUNS * o.nwg);
-        }
+        if (whole && o.nwg <= RBFFD_STEP_TILES) o.ord = b.take<int4>(2 * o.nwg + 1);
     } else {
         o.st_curl = b.take<int32_t>(o.Nt * o.n);
         o.st_hv = o.nh > 0 ? b.take<int32_t>(o.Nt * o.nh) : nullptr;
@@ -151,6 +148,8 @@ int64_t layout_arena(rbffd_plan* p, char* base, int64_t* ws, int64_t* adj_ws) {
         (void)keep;
     }
     p->gk = p->K > 1 ? b.take<float>(p->K) : nullptr;
+    if (can_step_whole(p) && p->opH.nwg <= RBFFD_STEP_TILES)   // as OpBlock::ord
+        p->opH.flags = b.take<uint64_t>(RBFFD_STEP_RUNS * p->opH.nwg);
     if (ws) *ws = setup_ws_bytes(p);
     if (adj_ws) {
         const int64_t fb = field_elem_bytes(p->p.fdtype) > 4 ? 8 : 4;
