@@ -593,7 +593,8 @@ def main():
             if not args.no_tune:
                 sc.autotune(stc, reps=20)
                 stc = sc.state(wc.E0, wc.H0)
-            sc.run(stc, 20, use_graph=True)
+            # enough steps for a graph: the process's first capture takes some 4 ms
+            sc.run(stc, 256, use_graph=True)
             stc = sc.state(wc.E0, wc.H0)
             torch.cuda.synchronize()
             e0.record(stream)
