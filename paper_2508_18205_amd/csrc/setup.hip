@@ -649,7 +649,7 @@ __global__ __launch_bounds__(1024) void k_weights(WArgs a) {
 // column, which hands over the column.  Columns left of the pivot are not
 // updated any more (the loop over column blocks is unrolled).
 // Measured, ms for the hyperviscosity systems of 160k 2D nodes (86 columns) /
-// 91k 3D nodes (107) / the curl systems of 160k 2D nodes (42): 16.6 / 13.4 / 2.5;
+// 91k 3D nodes (107) / the curl systems of 160k 2D nodes (42): 17.2 / 14.0 / 3.1;
 // the same results from 256 threads with two barriers per column and LDS
 // shuffles 27.7 / 28.5 / 6.7.  (Comparing only the leading 13 bits of the
 // candidates and a Newton reciprocal take 14.9 / 12.1, but other roundings.)
